@@ -95,6 +95,12 @@ __device__ __forceinline__ void load_lds16_nt(const void* gsrc, void* lds_base) 
   __builtin_amdgcn_global_load_lds((glb_void_t*)gsrc, (lds_void_t*)lds_base, 16, 0, 2);
 }
 
+// 16 bytes per lane through a buffer descriptor straight into LDS at lds_base
+// + 16 * lane: per-lane and uniform byte offsets, zeros past the buffer's size.
+__device__ __forceinline__ void buf_load_lds16(__amdgpu_buffer_rsrc_t r, void* lds_base, int voff, int soff) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_t*)lds_base, 16, voff, soff, 0, 0);
+}
+
 // LDS read the compiler does not see as a memory access: it then cannot
 // conflate it with pending LDS-DMA writes (which would make it drain every
 // outstanding load).  The caller must wait with lds_wait() before using the

@@ -1,0 +1,44 @@
+"""GPU parity of the projections at the edges of their tiles, through the C ABI.
+
+A prefill of M rows and the decode steps after it run every projection of a
+layer on the kernel that M selects: up to 128 rows the streaming GEMM, above it
+the tiled one over the packed weights (128 x 128, 128 x 256 and 256 x 256 tiles).
+The bar is the bf16 parity bound of the other cases: the kernels accumulate the
+same products in the same order of k, whatever the tile.
+"""
+import numpy as np
+import pytest
+
+import workloads as W
+from tests import parity as P
+
+pytestmark = pytest.mark.gpu
+
+
+def _small(n_prompts, group, prompt_len, vocab=32000, steps=2):
+    wl = W.workload("small").replace(gain_jitter=0.05, n_prompts=n_prompts, group=group, prompt_len=prompt_len)
+    wl.senior.n_layers, wl.junior.n_layers = 1, 1
+    wl.senior.vocab = wl.junior.vocab = vocab
+    wl.sample.max_new = steps
+    return wl
+
+
+# (prompts, responses, prompt length, vocabulary, sequences checked): rows of
+# the prefill are prompts x (length - 1), of a step prompts x responses
+CASES = [
+    (1, 1, 130, 32000, None),            # 129 rows: a second tile of one row; steps of one row
+    (3, 11, 86, 32000, [0, 20, 32]),     # 255 rows; steps of 33 rows (two 32-row blocks, one row used)
+    (2, 1, 130, 32000, None),            # 258 rows
+    (2, 1, 1030, 32000, [1]),            # 2058 rows: 256 x 256 tiles with a ragged last row
+    (5, 26, 9, 32001, [0, 70, 129]),     # 40 rows; steps of 130 rows, logits of an odd vocabulary in tiles
+    (3, 43, 3, 32000, [5, 128]),         # steps of 129 rows, logits of a 128 x 256 tiled head
+    (3, 32, 3, 31972, [5, 95]),          # steps of 96 rows, a last vocabulary block of 4 entries
+]
+
+
+@pytest.mark.parametrize("n_prompts,group,prompt_len,vocab,rows", CASES)
+def test_projection_tile_edges(n_prompts, group, prompt_len, vocab, rows):
+    P.log(f"case GEMM shapes: {n_prompts} prompts of {prompt_len} tokens x {group}, V {vocab}")
+    p = P.run(_small(n_prompts, group, prompt_len, vocab), logits_at=(1, 2), seq_subset=rows)
+    P.check(p, P.TOL_BF16)
+    assert np.isfinite(p.out["logprob"]).all()
