@@ -78,7 +78,7 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(const bf16_t* __restr
 
 // Both operands are loaded NS - 1 chunks ahead of the arithmetic: weights
 // (from HBM) into a ring of NS register sets, activations (L2-resident) into
-// an NS-stage LDS ring.  Iteration c issues A(c + NS - 1) then W(c + NS - 1).
+// an NS-stage LDS ring.  Chunk c issues A(c + NS - 1) then W(c + NS - 1).
 // Vector loads retire in order, so the two rings must be equally deep: a
 // wait for an activation stage also waits for every weight load issued
 // before it.
@@ -91,9 +91,12 @@ struct StreamShape {
   static constexpr int RPI = 64 / NPC;               // rows per 1 KB DMA instruction
   static constexpr int ASTAGE = BM * RB;             // bytes of one activation stage
   static constexpr int NA = BM / (RPI * SNW);        // activation DMA instructions per wave per chunk
-  static constexpr int NWL = 4;                      // weight loads per wave per chunk
+  static constexpr int NL = NA + 4;                  // all loads per wave per chunk (4 weight fragments)
+  static constexpr int NMF = 4 * MB * PARTS;         // MFMAs per wave per chunk
+  static constexpr bool SPREAD = MB > 1;             // loads between the MFMAs (at most 32 rows: first, the stream
+                                                     // is bound by HBM and gains from the earlier issue)
   static constexpr int DW = NS - 1;                  // chunks in flight ahead of the arithmetic
-  static constexpr int WAIT = (DW - 1) * (NA + NWL); // vmcnt once A(c) and W(c) have landed
+  static constexpr int WAIT = (DW - 1) * NL;         // vmcnt once A(c) and W(c) have landed
   static_assert(NS >= 2, "ring of register sets and LDS stages");
   static_assert(NS * ASTAGE <= 160 * 1024, "LDS ring");
   static_assert(WAIT < 64, "vmcnt range");
@@ -114,13 +117,14 @@ __global__ __launch_bounds__(256) void gemm_stream_kernel(
     float* __restrict__ out, int ldo, long split_stride, SampleEpiArgs smp) {
   using G = StreamShape<MB, NS, A16>;
   constexpr int PARTS = G::PARTS, NPC = G::NPC;
+  constexpr bool SWAP = EPI == EPI_SAMPLE || EPI == EPI_SWIGLU;   // weights as the MFMA's row operand
   __shared__ __attribute__((aligned(1024))) unsigned char ring[NS * G::ASTAGE];
   // EPI_SAMPLE: an item's output tile (BM rows x 128 vocabulary entries,
   // padded rows) on its way from the MFMA layout to one row per thread pair
   constexpr int TSTR = 128 + 4;
   __shared__ __attribute__((aligned(16))) float tile[EPI == EPI_SAMPLE ? G::BM * TSTR : 1];
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 5, c32 = lane & 31;
   const int nch = K / SBK;
   const int n_items = n_groups * S;
@@ -145,29 +149,29 @@ __global__ __launch_bounds__(256) void gemm_stream_kernel(
   // Activation DMA: instruction i of wave w covers tile rows
   // r0 + RPI SNW i .. +RPI - 1 (r0 = RPI w + lane / NPC; a row is NPC 16-byte
   // pieces: split format 8 hi and 8 lo pieces, fp16 8 pieces); physical piece
-  // lane % NPC holds logical piece (lane % NPC) ^ (row % NPC).
-  const int r0 = G::RPI * wave + lane / NPC;
-  const int lc = (lane % NPC) ^ (r0 % NPC);
-  const size_t lda = (size_t)K * PARTS;                    // row stride (2-byte elements)
+  // lane % NPC holds logical piece (lane % NPC) ^ (row % NPC).  Rows past M lie
+  // outside the descriptor and read as zeros.
+  const int lda = K * PARTS * 2;                           // row bytes
+  const __amdgpu_buffer_rsrc_t ar = buf_rsrc(A, (uint32_t)M * (uint32_t)lda);
   const __amdgpu_buffer_rsrc_t wr = buf_rsrc(Wp, (uint32_t)((size_t)nblk * (K / 16) * 1024));
   const int kfr = K / 16;                                  // fragments per 32-row block
+  int avoff[G::NA];
+#pragma unroll
+  for (int i = 0; i < G::NA; ++i) {
+    const int r = G::RPI * (SNW * i + wave) + lane / NPC;
+    avoff[i] = r * lda + (((lane % NPC) ^ (r % NPC)) * 16);
+  }
 
   u32x4_t wb[NS][4];
-  auto issue_a = [&](const Cursor& u, int stage) {
+  // load i of the chunk at u: activations into LDS stage `stage`, then weights into w
+  auto load = [&](const Cursor& u, int stage, u32x4_t (&w)[4], int i) {
     const int kc = u.s * cps + u.c;
-    unsigned char* st = ring + stage * G::ASTAGE;
-#pragma unroll
-    for (int i = 0; i < G::NA; ++i) {
-      const bf16_t* src = A + (size_t)min(r0 + G::RPI * SNW * i, M - 1) * lda + (size_t)kc * PARTS * SBK + lc * 8;
-      load_lds16(src, st + 4 * (SNW * i + wave) * 256);
+    if (i < G::NA) {
+      buf_load_lds16(ar, ring + stage * G::ASTAGE + (SNW * i + wave) * 1024, avoff[i], kc * G::RB);
+    } else {
+      const int nb = min(u.grp * SNW + wave, nblk - 1);
+      w[i - G::NA] = buf_load16_nt(wr, lane * 16, (nb * kfr + 4 * kc + i - G::NA) * 1024);
     }
-  };
-  auto issue_w = [&](const Cursor& u, u32x4_t (&w)[4]) {
-    const int kc = u.s * cps + u.c;
-    const int nb = min(u.grp * SNW + wave, nblk - 1);
-    const int base = (nb * kfr + 4 * kc) * 1024 + lane * 16;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) w[j] = buf_load16_nt(wr, base + j * 1024, 0);
   };
   // keeps the loads issued so far above the arithmetic of this chunk and
   // makes the compiler wait for this chunk's weights here, not earlier
@@ -200,16 +204,26 @@ __global__ __launch_bounds__(256) void gemm_stream_kernel(
 #pragma unroll
       for (int part = 0; part < PARTS; ++part) lds_fence_value(f[mb][part]);
   };
-  // one chunk = 4 k-steps; the A fragments of k-step j + 1 are read while the
+  // One chunk = 4 k-steps; the A fragments of k-step j + 1 are read while the
   // MFMAs of k-step j run (split format: high parts of every block, then low
-  // parts, so consecutive MFMAs never share an accumulator when MB > 1)
-  auto compute = [&](int stage, u32x4_t (&w)[4]) {
+  // parts, so consecutive MFMAs never share an accumulator when MB > 1).  The
+  // loads of the chunk DW ahead (at lu, into stage ls and registers lw) go out
+  // one by one between the MFMAs: a load takes 16 clocks of the compute unit's
+  // address path, and a wave that issues its 8 to 12 loads at once stands still
+  // for 500 to 770 clocks (split format, 128 rows: 2120 clocks per chunk with
+  // the loads first, 1320 with them spread; the MFMAs alone take 1024).
+  auto compute = [&](int stage, u32x4_t (&w)[4], const Cursor& lu, int ls, u32x4_t (&lw)[4]) {
     const uint32_t st = ring_addr + (uint32_t)(stage * G::ASTAGE);
     u32x4_t fa[MB][PARTS], fb[MB][PARTS];
+    if (!G::SPREAD) {
+#pragma unroll
+      for (int i = 0; i < G::NL; ++i) load(lu, ls, lw, i);
+    }
     read_a(st, 0, fa);
     pin(w);
     lds_wait();
     fence_a(fa);
+    int mi = 0, li = 0;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       u32x4_t (&cur)[MB][PARTS] = (j & 1) ? fb : fa;
@@ -219,12 +233,25 @@ __global__ __launch_bounds__(256) void gemm_stream_kernel(
       for (int part = 0; part < PARTS; ++part)
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
+          // results: rows of the tile by lane for split-K partials and logits
+          // (64-lane stores of two whole 128-byte row pieces); transposed, four
+          // consecutive columns of one row per lane, for the other epilogues
+          const u32x4_t x = SWAP ? w[j] : cur[mb][part], y = SWAP ? cur[mb][part] : w[j];
           if (A16)
-            acc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8_t, cur[mb][part]),
-                                                             __builtin_bit_cast(f16x8_t, w[j]), acc[mb], 0, 0, 0);
+            acc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8_t, x),
+                                                             __builtin_bit_cast(f16x8_t, y), acc[mb], 0, 0, 0);
           else
-            acc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, cur[mb][part]),
-                                                              __builtin_bit_cast(bf16x8_t, w[j]), acc[mb], 0, 0, 0);
+            acc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, x),
+                                                              __builtin_bit_cast(bf16x8_t, y), acc[mb], 0, 0, 0);
+          ++mi;
+#pragma unroll
+          for (int rep = 0; rep < G::NL; ++rep)
+            if (G::SPREAD && li < G::NL && li * G::NMF < mi * G::NL) {
+              __builtin_amdgcn_sched_barrier(0);
+              load(lu, ls, lw, li);
+              ++li;
+              __builtin_amdgcn_sched_barrier(0);
+            }
         }
       if (j < 3) {
         lds_wait();
@@ -261,15 +288,21 @@ __global__ __launch_bounds__(256) void gemm_stream_kernel(
       }
       // scores s = (z + b 1[v = eos]) / T into the tile
       const float inv_t = 1.f / smp.temp;
-      const float eb = u.grp * 128 + wave * 32 + c32 == smp.eos_id ? smp.eos_bias * inv_t : 0.f;
+      const float eb = smp.eos_bias * inv_t;
 #pragma unroll
-      for (int mb = 0; mb < MB; ++mb)
+      for (int mb = 0; mb < MB; ++mb) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int m = mb * 32 + 8 * (i >> 2) + 4 * g + (i & 3);
-          tile[m * TSTR + wave * 32 + c32] = fmaf(acc[mb][i], inv_t, eb);
-          acc[mb][i] = 0.f;
+        for (int i = 0; i < 4; ++i) {
+          const int n = wave * 32 + 8 * i + 4 * g, e0 = smp.eos_id - u.grp * 128 - n;
+          float4 v;
+          v.x = fmaf(acc[mb][4 * i], inv_t, e0 == 0 ? eb : 0.f);
+          v.y = fmaf(acc[mb][4 * i + 1], inv_t, e0 == 1 ? eb : 0.f);
+          v.z = fmaf(acc[mb][4 * i + 2], inv_t, e0 == 2 ? eb : 0.f);
+          v.w = fmaf(acc[mb][4 * i + 3], inv_t, e0 == 3 ? eb : 0.f);
+          *reinterpret_cast<float4*>(tile + (mb * 32 + c32) * TSTR + n) = v;
         }
+        acc[mb] = f32x16_t{};
+      }
       __syncthreads();
       if (work) {
         // the four scores of quad q of this half (-inf past the vocabulary),
@@ -332,35 +365,51 @@ __global__ __launch_bounds__(256) void gemm_stream_kernel(
       return;
     }
     if (EPI == EPI_SWIGLU) {
-      // columns c < 16 of a block are gate sums, c + 16 the matching up sums
-      // (pair-interleaved packing); output column 16 nb + c, in the input's
-      // format (fp16, or split)
-      const int j = nb * 16 + (c32 & 15);
+      // element 4 i + e is column 8 i + 4 g + e of the block: gate sums in
+      // columns 0 .. 15, the matching up sums in 16 .. 31 (pair-interleaved
+      // packing), both in this lane; four consecutive output columns at a time
+      // in the input's format (fp16, or split)
 #pragma unroll
-      for (int mb = 0; mb < MB; ++mb)
+      for (int mb = 0; mb < MB; ++mb) {
+        const int m = mb * 32 + c32;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const float v = acc[mb][i];
-          const float up = __shfl_xor(v, 16, 64);
-          const int m = mb * 32 + 8 * (i >> 2) + 4 * g + (i & 3);
-          if (m < M && c32 < 16 && j < ldo) {
-            if (A16) reinterpret_cast<uint16_t*>(out)[(size_t)m * ldo + j] = f2h(silu_f(v) * up);
-            else split_store(reinterpret_cast<bf16_t*>(out) + (size_t)m * 2 * ldo, j, silu_f(v) * up);
+        for (int i = 0; i < 2; ++i) {
+          const int j = nb * 16 + 8 * i + 4 * g;
+          if (m < M && j < ldo) {
+            float y[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) y[e] = silu_f(acc[mb][4 * i + e]) * acc[mb][8 + 4 * i + e];
+            if (A16) {
+              *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(out) + (size_t)m * ldo + j) =
+                  make_uint2((uint32_t)f2h(y[0]) | ((uint32_t)f2h(y[1]) << 16),
+                             (uint32_t)f2h(y[2]) | ((uint32_t)f2h(y[3]) << 16));
+            } else {
+#pragma unroll
+              for (int e = 0; e < 4; ++e) split_store(reinterpret_cast<bf16_t*>(out) + (size_t)m * 2 * ldo, j + e, y[e]);
+            }
           }
-          acc[mb][i] = 0.f;
         }
+        acc[mb] = f32x16_t{};
+      }
       return;
     }
-    float* o = out + (size_t)u.s * split_stride;
+    // Rows past M lie outside the descriptor, columns past N are sent there:
+    // the stores need no branches (64 guarded stores took 4400 clocks, 64
+    // unguarded ones 1800).  They are written through (sc0 sc1): the partials
+    // are read by other XCDs, and written back only at the end of the launch
+    // they would cost 1 us of it (15.7 MB of QKV partials: 4.8 -> 3.8 us).
+    const __amdgpu_buffer_rsrc_t orr = buf_rsrc(out + (size_t)u.s * split_stride, (uint32_t)M * (uint32_t)ldo * 4u);
     const int n = nb * 32 + c32;
+    const uint32_t o0 = n < N ? ((uint32_t)(4 * g) * (uint32_t)ldo + (uint32_t)n) * 4u : 0x80000000u;
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
+    for (int mb = 0; mb < MB; ++mb) {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int m = mb * 32 + 8 * (i >> 2) + 4 * g + (i & 3);
-        if (m < M && n < N) o[(size_t)m * ldo + n] = acc[mb][i];
-        acc[mb][i] = 0.f;
-      }
+      for (int i = 0; i < 16; ++i)
+        __builtin_amdgcn_raw_buffer_store_b32(
+            __float_as_uint(acc[mb][i]), orr,
+            (int)(o0 + (uint32_t)(mb * 32 + 8 * (i >> 2) + (i & 3)) * (uint32_t)ldo * 4u), 0, 17);
+      acc[mb] = f32x16_t{};
+    }
   };
 
   // Every item's chunk count is a multiple of NS (the host guarantees
@@ -370,8 +419,8 @@ __global__ __launch_bounds__(256) void gemm_stream_kernel(
   set_item(la, blockIdx.x);
 #pragma unroll
   for (int d = 0; d < G::DW; ++d) {
-    issue_a(la, d);
-    issue_w(la, wb[d]);
+#pragma unroll
+    for (int i = 0; i < G::NL; ++i) load(la, d, wb[d], i);
     advance(la);
   }
   for (int item = blockIdx.x; item < n_items; item += grid) {
@@ -382,10 +431,8 @@ __global__ __launch_bounds__(256) void gemm_stream_kernel(
         wait_vmcnt<G::WAIT>();          // A(c) and W(c) of this wave have landed
         lds_wait();                     // and its LDS reads of the previous chunk are done
         __builtin_amdgcn_s_barrier();   // ... in every wave: A(c) is complete, stage c - 1 is free
-        issue_a(la, (u + G::DW) % NS);
-        issue_w(la, wb[(u + G::DW) % NS]);
+        compute(u, wb[u], la, (u + G::DW) % NS, wb[(u + G::DW) % NS]);
         advance(la);
-        compute(u, wb[u]);
       }
     }
     epilogue(cp);
@@ -405,7 +452,10 @@ __global__ __launch_bounds__(256) void gemm_stream_kernel(
 
 template <int MB, bool A16, int EPI>
 hipError_t run_stream(const GemmStreamArgs& a, int grid, hipStream_t st) {
-  constexpr int NS = kStreamStages;
+  // 128 rows in split format: two stages (64 KB of LDS instead of 128) leave
+  // room for the other model's GEMM on the compute unit (Qwen-shaped pair,
+  // 128 rows: 5.94 -> 5.87 ms per step; alone they are as fast)
+  constexpr int NS = !A16 && MB == 4 ? 2 : kStreamStages;
   hipLaunchKernelGGL((gemm_stream_kernel<MB, NS, A16, EPI>), dim3(grid), dim3(64 * SNW), 0, st,
                      (const bf16_t*)a.A, (const bf16_t*)a.Wp, a.M, a.N, a.K, a.n_groups, a.S, a.cps, a.out, a.ldo,
                      a.split_stride, a.smp);
@@ -428,7 +478,7 @@ size_t packed_weight_bytes(int N, int K) { return (size_t)((N + 31) / 32) * 32 *
 
 bool stream_gemm_ok(int M, int N, int K) {
   return M >= 1 && M <= kStreamMaxRows && K % (SBK * kStreamStages) == 0 && N >= 1 &&
-         packed_weight_bytes(N, K) < ((size_t)1 << 31);
+         packed_weight_bytes(N, K) < ((size_t)1 << 31) && (size_t)kStreamMaxRows * K * 4 < ((size_t)1 << 31);
 }
 
 hipError_t launch_pack_weights(const void* W, int N, int K, int pair_rows, bool to_f16, void* out, hipStream_t st) {
