@@ -173,7 +173,9 @@ struct SampleArgs {
   const int32_t* owner; const int32_t* t; const int32_t* done;   // per sequence
   const int32_t* act;     // [R] sequence of each row
   float* partials;        // [R][n_chunks][5]
-  int chunk;              // vocab entries per chunk
+  int chunk;              // vocab entries per chunk (4096)
+  // raw logits by sequence [n_seqs][V], rows act[r] (debug; NULL: none)
+  float* dbg_sen; float* dbg_jun;
 };
 hipError_t launch_sample_partials(const SampleArgs& a, int n_chunks, hipStream_t st);
 
@@ -212,7 +214,7 @@ hipError_t launch_sample_finish(const FinishArgs& a, hipStream_t st);
 // row not done before the step (row_done[r] == 0), with y = tok[act[r]]
 // the token the step emitted, out[act[r]][0 .. 2] = (-log p_jun(y),
 // sum_v min(p_sen, p_jun), KL(p_sen || p_jun)).  lse: [R][n_chunks][4],
-// sums: [R][n_chunks][2] of scratch; chunk vocabulary entries per chunk.
+// sums: [R][n_chunks][2] of scratch; chunk vocabulary entries per chunk (4096).
 struct ScoreArgs {
   const float* z_sen; const float* z_jun; int R, V;
   const int32_t* act; const int32_t* row_done; const int32_t* tok;
@@ -298,10 +300,6 @@ struct GatherRowsArgs {
   int32_t* row_tok; int32_t* row_slot; int32_t* row_pos; int32_t* row_done;
 };
 hipError_t launch_gather_rows(const GatherRowsArgs& a, hipStream_t st);
-
-// dst[act[r]][0 .. V) = src[r][0 .. V) for rows 0 .. R-1 (debug logits by sequence).
-hipError_t launch_scatter_rows(const float* src, const int32_t* act, int R, int V, float* dst, hipStream_t st);
-
 
 // true when the MFMA attention kernel covers this (dtype, head_dim, group size)
 bool attention_has_mfma(int dt, int hd, int gqa);

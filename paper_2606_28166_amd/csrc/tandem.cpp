@@ -719,12 +719,11 @@ tandem_status record_step(tandem_handle* h, const int32_t* forced, const tandem_
     sa.key0 = h->key0; sa.key1 = h->key1;
     sa.owner = h->owner; sa.t = h->t; sa.done = h->done; sa.act = h->act;
     sa.partials = h->partials; sa.chunk = kVocabChunk;
-    TIMED(TANDEM_K_SAMPLE, launch_sample_partials(sa, h->plan.n_chunks, st));
     if (dbg) {
-      if (dbg->logits_senior) HIPCHK(launch_scatter_rows(h->m[0].logits, h->act, R, V, dbg->logits_senior, st));
-      if (dbg->logits_junior && h->nm == 2)
-        HIPCHK(launch_scatter_rows(h->m[1].logits, h->act, R, V, dbg->logits_junior, st));
+      sa.dbg_sen = dbg->logits_senior;
+      sa.dbg_jun = h->nm == 2 ? dbg->logits_junior : nullptr;
     }
+    TIMED(TANDEM_K_SAMPLE, launch_sample_partials(sa, h->plan.n_chunks, st));
   }
   fa.z_sen = h->m[0].logits; fa.R = R; fa.V = V; fa.act = h->act;
   fa.temp = h->smp.temperature; fa.eos_id = h->smp.eos_id; fa.eos_bias_sen = h->smp.eos_bias_senior;
