@@ -262,8 +262,8 @@ struct tandem_handle {
   // runs on a second stream forked from and joined back into `stream`.
   hipStream_t side = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
-  // one event per layer of each model, recorded after that layer's FFN-input
-  // norm (the two streams' attentions take turns, see forward_pair)
+  // one event per layer of each model, recorded after that layer's attention
+  // (the two streams' attentions take turns, see forward_pair)
   std::vector<hipEvent_t> ev_att[2];
   // Step graphs are captured on a stream of the library's own (the caller's
   // may be the legacy null stream, which cannot be captured) and replayed on
@@ -522,7 +522,7 @@ tandem_status forward_embed(tandem_handle* h, Model& m, const FwdRows& fr, hipSt
 }
 
 // att_wait: an event the layer's attention waits for first (NULL: none);
-// att_done: recorded after the FFN-input norm launch (NULL: none).
+// att_done: recorded after the attention launch (NULL: none).
 tandem_status forward_layer(tandem_handle* h, Model& m, int l, const FwdRows& fr, hipStream_t st,
                             hipEvent_t att_wait = nullptr, hipEvent_t att_done = nullptr) {
   const tandem_model_cfg& c = m.cfg;
@@ -560,6 +560,7 @@ tandem_status forward_layer(tandem_handle* h, Model& m, int l, const FwdRows& fr
   }
   if (att_wait) HIPCHK(hipStreamWaitEvent(st, att_wait, 0));
   TIMED(TANDEM_K_ATTENTION, launch_attention(aa, st));
+  if (att_done) HIPCHK(hipEventRecord(att_done, st));   // the other model's next attention may start
 
   // the FFN's activations are fp16 when both its products have fp16 packed
   // copies (the streaming GEMM up to 128 rows, the tiled one above; the
@@ -568,8 +569,6 @@ tandem_status forward_layer(tandem_handle* h, Model& m, int l, const FwdRows& fr
   const bool last = l + 1 == c.n_layers;
   CALL(gemm(h, m, m.xa, L.w_o, L.p_o, R, d, att, EPI_PARTIAL, m.ws, &S, st));
   TIMED(TANDEM_K_OTHER, launch_resid_norm(dt, m.ws, S, (long)R * d, m.h, L.ffn_norm, c.rms_eps, m.xa, R, d, f16, st));
-  // the other model's next attention may start (see forward_pair)
-  if (att_done) HIPCHK(hipEventRecord(att_done, st));
 
   CALL(gate_up(h, m, L, R, st));
   CALL(gemm(h, m, m.xf, L.w_down, L.p_down, R, d, c.ffn_dim, EPI_PARTIAL, m.ws, &S, st, f16));
@@ -634,15 +633,19 @@ tandem_status forward(tandem_handle* h, int i, const FwdRows& fr, bool lm_head, 
 // the senior on the main stream, joined before anything that reads either.
 // The two models' decode attentions are bound by HBM bandwidth, their
 // projections mostly by latency: the step runs both forwards on two streams
-// and lets the attention launches take turns, so each model's attention runs
-// beside the other model's projections rather than beside its attention.
-// The turn order interleaves the layers evenly (layer l of a model with L
-// layers at (l + 1/2) / L); an attention waits until the layer before it in
-// that order, of the other model, has run its attention, O projection and
-// FFN-input norm: those two kernels of the senior, on its critical path, are
-// then not slowed by the junior's attention grid beside them (the O
-// projection and norm of a model take about 25 us alone and 80 us beside the
-// other model's attention).
+// and, where an attention launch fills the device (two workgroups or more per
+// compute unit in both models), lets the attention launches take turns, so
+// each model's attention runs beside the other model's projections rather than
+// beside its attention.  The turn order interleaves the layers evenly (layer l
+// of a model with L layers at (l + 1/2) / L); an attention waits for the
+// attention before it in that order, of the other model.  Qwen-shaped pair at
+// full depth, 128 rows, ms per step with turns / without / with turns that pass
+// only after the FFN-input norm: 5.64 / 5.77 / 5.90 at 300 positions, 10.27 /
+// 10.48 / 10.38 at 1100.  A smaller grid leaves compute units free, and the
+// edges between the streams (about 5 us each) only cost: 32 rows 3.73 with,
+// 3.70 without; 64 rows of the small pair 0.575 with, 0.559 without.  Prompt
+// rows take no turns either (ragged prompts of the small pair 7.44 with, 7.34
+// without).
 //
 // With the sampling inside the LM heads (fused), the step's Gumbel noise is
 // generated first on the junior's stream (whose chain is the shorter one) and
@@ -666,6 +669,8 @@ tandem_status forward_pair(tandem_handle* h, const FwdRows& fr, bool lm_head, bo
     const int L[2] = {ms[0]->cfg.n_layers, ms[1]->cfg.n_layers};
     CALL(forward_embed(h, *ms[0], fr, sts[0]));
     CALL(forward_embed(h, *ms[1], fr, sts[1]));
+    bool turns = fr.done != nullptr;
+    for (const Model* m : ms) turns = turns && (long)m->cfg.n_kv_heads * fr.R >= 2L * h->n_cu;
     int next[2] = {0, 0}, prev_model = -1, prev_layer = -1;
     while (next[0] < L[0] || next[1] < L[1]) {
       // the model whose next layer comes first in the interleaved order
@@ -674,8 +679,8 @@ tandem_status forward_pair(tandem_handle* h, const FwdRows& fr, bool lm_head, bo
       else if (next[1] >= L[1]) i = 0;
       else i = (2 * next[0] + 1) * (long)L[1] <= (2 * next[1] + 1) * (long)L[0] ? 0 : 1;
       const int l = next[i]++;
-      hipEvent_t wait = (prev_model >= 0 && prev_model != i) ? h->ev_att[prev_model][prev_layer] : nullptr;
-      CALL(forward_layer(h, *ms[i], l, fr, sts[i], wait, h->ev_att[i][l]));
+      hipEvent_t wait = (turns && prev_model >= 0 && prev_model != i) ? h->ev_att[prev_model][prev_layer] : nullptr;
+      CALL(forward_layer(h, *ms[i], l, fr, sts[i], wait, turns ? h->ev_att[i][l] : nullptr));
       prev_model = i;
       prev_layer = l;
     }
