@@ -495,7 +495,10 @@ StreamPlan plan_stream_gemm(int M, int N, int K, int n_cu, size_t ws_floats, int
   // to at most n_cu workgroups, each item costs its chunks plus about two for
   // its epilogue and pipeline refill; K slices > 1 also pay for the partial
   // tiles the consumer reads back (in 32 KB-per-unit chunks spread over the
-  // device) and, for SwiGLU, for the separate pass that applies it.
+  // device) and, for SwiGLU, for the separate pass that applies it: a launch of
+  // its own, about 12 chunk times (64 rows of the small pair 0.552 ms per step
+  // with 4, 0.558 with 8, 0.530 with 12 or 20; 16 rows of the Qwen-shaped senior
+  // 0.343, 0.343, 0.332).
   const int nch = K / SBK;
   const int groups = (N + 127) / 128;
   const int smax = mode == kPlanStore ? 1 : std::min(kSplitMaxStream, nch / kStreamStages);
@@ -510,7 +513,7 @@ StreamPlan plan_stream_gemm(int M, int N, int K, int n_cu, size_t ws_floats, int
     double cost = (double)((items + n_cu - 1) / n_cu) * (cps + 2);
     if (S > 1) {
       cost += (double)S * M * N * 4 / ((double)n_cu * 32768);
-      if (mode == kPlanSwiglu) cost += 4 + (double)S * M * N * 4 / ((double)n_cu * 16384);
+      if (mode == kPlanSwiglu) cost += 12 + (double)S * M * N * 4 / ((double)n_cu * 16384);
     }
     if (cost < best) {
       best = cost;
