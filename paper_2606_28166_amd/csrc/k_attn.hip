@@ -1,8 +1,8 @@
 // Grouped-query attention of one new query position per row over that row's
-// KV cache (decode), also used for prompt rows (each prompt token attends to
-// positions 0..its own position of the prompt's cache).
+// KV cache (decode), and of prompt rows (each prompt token attends to positions
+// 0..its own position of the prompt's cache; see attn_prompt_kernel).
 //
-// bf16 path (HD in {64, 128}): one workgroup per (kv head, row); its four
+// bf16 decode (HD in {64, 128}): one workgroup per (kv head, row); its four
 // waves take interleaved 16-position chunks of the tiled cache and keep
 // their own online softmax, merged through LDS at the end.  The products
 // run on MFMA:
@@ -65,11 +65,11 @@ struct Half {
   u32x4_t r[HD / 32];
 };
 
-template <int HD, bool NT = true>
+template <int HD>
 __device__ __forceinline__ void load_half(Half<HD>& h, __amdgpu_buffer_rsrc_t rs, int chunk, int lane) {
   const int base = chunk * 32 * HD + lane * 16;   // bytes: 16 positions x HD x 2
 #pragma unroll
-  for (int j = 0; j < HD / 32; ++j) h.r[j] = NT ? buf_load16_nt(rs, base + j * 1024, 0) : buf_load16(rs, base + j * 1024, 0);
+  for (int j = 0; j < HD / 32; ++j) h.r[j] = buf_load16_nt(rs, base + j * 1024, 0);
 }
 
 // Orders the loads issued so far before everything that follows and ties h
@@ -89,14 +89,11 @@ struct AttnState {
   f32x4_t o[HD / 16];             // O[head 4g + i][dim 16 db + c16]
 };
 
-// ctx: this lane's query column attends positions < ctx; ctx_max: positions
-// >= ctx_max hold stale cache contents.  GUARD: a column may see a chunk with
-// no position it attends before any it does (several query rows per
-// workgroup); its running max then stays -inf and nothing is added.
+// ctx: the row attends positions < ctx (later ones hold stale cache contents).
 // First half of a chunk: scores of its 16 positions from the K tile, the
 // online-softmax update and the rescaling of the accumulator; returns the
 // probabilities as split bf16 operands of the value product.
-template <int HD, bool GUARD>
+template <int HD>
 __device__ __forceinline__ void attend_scores(AttnState<HD>& st, const Half<HD>& k, const bf16x8_t* qh,
                                               const bf16x8_t* ql, int p0, int ctx, float scale, int g, s16x4_t& ph,
                                               s16x4_t& pl) {
@@ -117,11 +114,10 @@ __device__ __forceinline__ void attend_scores(AttnState<HD>& st, const Half<HD>&
   mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
   mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
   const float m_new = fmaxf(st.m_run, mx);
-  const bool none = GUARD && m_new == -INFINITY;
-  const float alpha = none ? 1.f : exp2f(st.m_run - m_new);
+  const float alpha = exp2f(st.m_run - m_new);
   float pr[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) pr[i] = none ? 0.f : exp2f(s[i] - m_new);
+  for (int i = 0; i < 4; ++i) pr[i] = exp2f(s[i] - m_new);
   st.l_run = st.l_run * alpha + ((pr[0] + pr[1]) + (pr[2] + pr[3]));
   st.m_run = m_new;
   split4(pr, ph, pl);
@@ -140,14 +136,14 @@ __device__ __forceinline__ void attend_scores(AttnState<HD>& st, const Half<HD>&
 // Second half of a chunk: the probabilities times its V tile.
 template <int HD>
 __device__ __forceinline__ void attend_values(AttnState<HD>& st, Half<HD>& v, s16x4_t ph, s16x4_t pl, int p0,
-                                              int ctx_max, int g) {
+                                              int ctx, int g) {
   constexpr int DC = HD / 32, DB = HD / 16;
   const int pg = p0 + 4 * g;
   // positions at or past the context hold stale cache contents: zero them so
   // that 0 * (stale) cannot produce NaN
-  if (p0 + 16 > ctx_max) {
+  if (p0 + 16 > ctx) {
     // keep the first nv of this lane's four positions (16 bits each)
-    const int nv = min(max(ctx_max - pg, 0), 4);
+    const int nv = min(max(ctx - pg, 0), 4);
     const uint64_t keep = nv == 4 ? ~0ull : (1ull << (16 * nv)) - 1ull;
     const uint32_t klo = (uint32_t)keep, khi = (uint32_t)(keep >> 32);
 #pragma unroll
@@ -168,31 +164,24 @@ __device__ __forceinline__ void attend_values(AttnState<HD>& st, Half<HD>& v, s1
   }
 }
 
-// One workgroup's attention: query columns c = (row r0 + c / GQA, head
-// kh GQA + c % GQA) for c < NCOL (rows >= r0 + nr are unused columns) over
-// positions [16 c0, ctx_max) of one slot's tiled K/V plane of kv head kh;
-// column c attends the positions below its own limit (row_pos[row] + 1 when
-// row_pos_col is given, else ctx_max).  The four waves take interleaved
-// 16-position chunks with their own online softmax and leave their states
-// in LDS: sm_m[w][c] (running max, log2 units), sm_l[w][c] (sum of
-// exponentials), sm_o[(w NCOL + c) HD + d] (unnormalised weighted sums).
-// GUARD: some column may see a chunk with no position it attends.
-template <int HD, int GQA, int NCOL, bool GUARD, bool NT = true>
+// One workgroup's attention of one row: query columns c < GQA are the heads
+// kh GQA + c, over positions [0, ctx) of one slot's tiled K/V plane of kv head
+// kh.  The four waves take interleaved 16-position chunks with their own online
+// softmax and leave their states in LDS: sm_m[w][c] (running max, log2 units),
+// sm_l[w][c] (sum of exponentials), sm_o[(w GQA + c) HD + d] (unnormalised
+// weighted sums).
+template <int HD, int GQA>
 __device__ __forceinline__ void attend_block(const float* __restrict__ q, const bf16_t* __restrict__ kc,
                                              const bf16_t* __restrict__ vc, int ctx_stride, long slot_stride,
-                                             int slot, int kh, int r0, int nr, int c0, int ctx_max,
-                                             const int32_t* __restrict__ row_pos_col, int nq, float (*sm_m)[16],
+                                             int slot, int kh, int row, int ctx, int nq, float (*sm_m)[16],
                                              float (*sm_l)[16], float* sm_o, int pslot = 0, int lo16 = 0) {
   constexpr int DC = HD / 32;     // k-steps of the S product
   constexpr int DB = HD / 16;     // 16-dim blocks of the O product
-  static_assert(NCOL <= 16, "16 query columns per workgroup");
+  static_assert(GQA <= 16, "16 query columns per workgroup");
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: the chunk branches stay scalar
   const int g = lane >> 4, c16 = lane & 15;
-  const int ri = c16 / GQA, hq = c16 % GQA;           // this lane's query column
-  const bool valid = c16 < NCOL && ri < nr;
-  const int rr = r0 + (valid ? ri : 0);
-  const int ctx = (valid && row_pos_col) ? row_pos_col[rr] + 1 : ctx_max;   // positions the column attends
+  const bool valid = c16 < GQA;                       // this lane's query column
   const size_t plane = (size_t)slot * slot_stride + (size_t)kh * ctx_stride * HD;
   const __amdgpu_buffer_rsrc_t kr_o = buf_rsrc(kc + plane, (uint32_t)ctx_stride * HD * 2);
   const __amdgpu_buffer_rsrc_t vr_o = buf_rsrc(vc + plane, (uint32_t)ctx_stride * HD * 2);
@@ -204,11 +193,11 @@ __device__ __forceinline__ void attend_block(const float* __restrict__ q, const 
   const __amdgpu_buffer_rsrc_t vr_p = buf_rsrc(vc + pplane, (uint32_t)ctx_stride * HD * 2);
   const float scale = 1.4426950408889634f / sqrtf((float)HD);   // log2(e) / sqrt(hd)
 
-  // Wave w owns chunks c0 + w, c0 + w + 4, ... of the stream.  The query is
+  // Wave w owns chunks w, w + 4, ... of the stream.  The query is
   // requested first and its first three chunks right after, behind a
   // compiler barrier, so that waiting for the query (the wait counter is in
   // issue order) leaves the chunks in flight.
-  const float* qp = q + ((size_t)rr * nq + kh * GQA + (valid ? hq : 0)) * HD + 8 * g;
+  const float* qp = q + ((size_t)row * nq + kh * GQA + (valid ? c16 : 0)) * HD + 8 * g;
   float4 qa[DC], qb[DC];
 #pragma unroll
   for (int dc = 0; dc < DC; ++dc) {
@@ -216,9 +205,9 @@ __device__ __forceinline__ void attend_block(const float* __restrict__ q, const 
     qb[dc] = *reinterpret_cast<const float4*>(qp + 32 * dc + 4);
   }
   asm volatile("" : : : "memory");
-  const int nchunk = ((ctx_max + 15) >> 4) - c0;
+  const int nchunk = (ctx + 15) >> 4;
   const int nmine = nchunk > wave ? (nchunk - wave + 3) >> 2 : 0;
-  auto chunk_at = [&](int i) { return c0 + wave + 4 * min(i, nmine - 1); };
+  auto chunk_at = [&](int i) { return wave + 4 * min(i, nmine - 1); };
   // Six half-chunk slots, three chunks: the K and V tiles of chunk i live in
   // slots 2 (i % 3) and 2 (i % 3) + 1, and each is refilled with the same
   // tile of chunk i + 3 as soon as it is consumed, so while a chunk is
@@ -232,12 +221,12 @@ __device__ __forceinline__ void attend_block(const float* __restrict__ q, const 
   auto kr = [&](int c) { return c < lo16 ? kr_p : kr_o; };
   auto vr = [&](int c) { return c < lo16 ? vr_p : vr_o; };
   Half<HD> h0, h1, h2, h3, h4, h5;
-  load_half<HD, NT>(h0, kr(src(0)), src(0), lane);
-  load_half<HD, NT>(h1, vr(src(0)), src(0), lane);
-  load_half<HD, NT>(h2, kr(src(1)), src(1), lane);
-  load_half<HD, NT>(h3, vr(src(1)), src(1), lane);
-  load_half<HD, NT>(h4, kr(src(2)), src(2), lane);
-  load_half<HD, NT>(h5, vr(src(2)), src(2), lane);
+  load_half<HD>(h0, kr(src(0)), src(0), lane);
+  load_half<HD>(h1, vr(src(0)), src(0), lane);
+  load_half<HD>(h2, kr(src(1)), src(1), lane);
+  load_half<HD>(h3, vr(src(1)), src(1), lane);
+  load_half<HD>(h4, kr(src(2)), src(2), lane);
+  load_half<HD>(h5, vr(src(2)), src(2), lane);
 
   // Q^T operand: column c16, k = dims 32dc + 8g .. +7 (zero for unused columns)
   bf16x8_t qh[DC], ql[DC];
@@ -264,13 +253,13 @@ __device__ __forceinline__ void attend_block(const float* __restrict__ q, const 
     const int p0 = 16 * chunk_at(j);
     s16x4_t ph, pl;
     pin_half<HD>(ks);
-    attend_scores<HD, GUARD>(st, ks, qh, ql, p0, ctx, scale, g, ph, pl);
+    attend_scores<HD>(st, ks, qh, ql, p0, ctx, scale, g, ph, pl);
     pin_half<HD>(ks);
-    load_half<HD, NT>(ks, kr(src(j + 3)), src(j + 3), lane);
+    load_half<HD>(ks, kr(src(j + 3)), src(j + 3), lane);
     pin_half<HD>(vs);
-    attend_values<HD>(st, vs, ph, pl, p0, ctx_max, g);
+    attend_values<HD>(st, vs, ph, pl, p0, ctx, g);
     pin_half<HD>(vs);
-    load_half<HD, NT>(vs, vr(src(j + 3)), src(j + 3), lane);
+    load_half<HD>(vs, vr(src(j + 3)), src(j + 3), lane);
   };
   // whole groups of three chunks as straight-line code, then the last < 3
   int i = 0;
@@ -296,7 +285,7 @@ __device__ __forceinline__ void attend_block(const float* __restrict__ q, const 
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int h = 4 * g + i;
-      if (h < NCOL) sm_o[(wave * NCOL + h) * HD + db * 16 + c16] = st.o[db][i];
+      if (h < GQA) sm_o[(wave * GQA + h) * HD + db * 16 + c16] = st.o[db][i];
     }
   __syncthreads();
 }
@@ -321,49 +310,29 @@ __device__ __forceinline__ void waves_merged(const float (*sm_m)[16], const floa
   }
 }
 
-// Workgroup (kv head, block of query rows).  Decode (ROWS = 1): one row per
-// workgroup, query columns = the GQA heads of the group.  Prompt rows (ROWS =
-// 16 / GQA): ROWS consecutive rows of one prompt share the workgroup, each
-// column with its own causal limit; the workgroup streams the positions its
-// last row attends, so a prompt's K/V is read once per ROWS rows rather than
-// once per row.  Row groups of at most 16 rows are split over sub_per_grp
-// workgroups of ROWS rows.
-template <int HD, int GQA, int ROWS>
+// One workgroup per (kv head, row), query columns = the GQA heads of the group:
+// decode rows, and prompt rows of 16-head groups (row_done NULL).
+template <int HD, int GQA>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void attn_mfma_kernel(
     const float* __restrict__ q, const bf16_t* __restrict__ kc, const bf16_t* __restrict__ vc,
     int ctx_stride, long slot_stride, const int32_t* __restrict__ row_slot,
     const int32_t* __restrict__ row_pos, const int32_t* __restrict__ row_done,
-    const int32_t* __restrict__ grp_row0, const int32_t* __restrict__ grp_n, int sub_per_grp,
     bf16_t* __restrict__ out, int nq) {
-  constexpr int NCOL = GQA * ROWS;
   __shared__ float sm_m[4][16];
   __shared__ float sm_l[4][16];
-  __shared__ float sm_o[4 * NCOL * HD];
-
-  const int kh = blockIdx.x, tid = threadIdx.x;
-  int r0 = blockIdx.y, nr = 1;
-  if (ROWS > 1) {
-    const int grp = blockIdx.y / sub_per_grp, sub = blockIdx.y % sub_per_grp;
-    r0 = grp_row0[grp] + sub * ROWS;
-    nr = min(ROWS, grp_n[grp] - sub * ROWS);
-    if (nr <= 0) return;
-  }
+  __shared__ float sm_o[4 * GQA * HD];
+  const int kh = blockIdx.x, r = blockIdx.y, tid = threadIdx.x;
   const int col0 = kh * GQA * HD;
-  if (ROWS == 1 && row_done && row_done[r0]) {
-    bf16_t* orow = out + (size_t)r0 * 2 * nq * HD;     // split-format activation row
+  bf16_t* orow = out + (size_t)r * 2 * nq * HD;      // split-format activation row
+  if (row_done && row_done[r]) {
     for (int e = tid; e < GQA * HD; e += 256) split_store(orow, col0 + e, 0.f);
     return;
   }
-  attend_block<HD, GQA, NCOL, (ROWS > 1)>(q, kc, vc, ctx_stride, slot_stride, row_slot[r0], kh, r0, nr, 0,
-                                          row_pos[r0 + nr - 1] + 1, ROWS > 1 ? row_pos : nullptr, nq, sm_m, sm_l,
-                                          sm_o);
-  for (int e = tid; e < NCOL * HD; e += 256) {
-    const int c = e / HD, d = e % HD;
-    if (c / GQA >= nr) continue;
+  attend_block<HD, GQA>(q, kc, vc, ctx_stride, slot_stride, row_slot[r], kh, r, row_pos[r] + 1, nq, sm_m, sm_l, sm_o);
+  for (int e = tid; e < GQA * HD; e += 256) {
     float M, num, den;
-    waves_merged<HD, NCOL>(sm_m, sm_l, sm_o, c, d, M, num, den);
-    bf16_t* orow = out + (size_t)(r0 + c / GQA) * 2 * nq * HD;
-    split_store(orow, col0 + (c % GQA) * HD + d, num / den);
+    waves_merged<HD, GQA>(sm_m, sm_l, sm_o, e / HD, e % HD, M, num, den);
+    split_store(orow, col0 + e, num / den);
   }
 }
 
@@ -372,7 +341,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
 // from the plane of the prompt's first sequence (pfx_slot) and [lo, pos] from
 // its own.  The G rows of a prompt are consecutive in the grid, so for each
 // kv head they run side by side on one XCD and read the prefix through its L2.
-template <int HD, int GQA, bool NT>
+template <int HD, int GQA>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void attn_rows_kernel(
     const float* __restrict__ q, const bf16_t* __restrict__ kc, const bf16_t* __restrict__ vc,
     int ctx_stride, long slot_stride, const int32_t* __restrict__ row_slot,
@@ -389,13 +358,202 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
     return;
   }
   const int lo = row_lo[r];
-  attend_block<HD, GQA, GQA, false, NT>(q, kc, vc, ctx_stride, slot_stride, row_slot[r], kh, r, 1, 0,
-                                        row_pos[r] + 1, nullptr, nq, sm_m, sm_l, sm_o, lo > 0 ? pfx_slot[r] : 0,
-                                        lo >> 4);
+  attend_block<HD, GQA>(q, kc, vc, ctx_stride, slot_stride, row_slot[r], kh, r, row_pos[r] + 1, nq, sm_m, sm_l, sm_o,
+                        lo > 0 ? pfx_slot[r] : 0, lo >> 4);
   for (int e = tid; e < GQA * HD; e += 256) {
     float M, num, den;
     waves_merged<HD, GQA>(sm_m, sm_l, sm_o, e / HD, e % HD, M, num, den);
     split_store(orow, col0 + e, num / den);
+  }
+}
+
+// Prompt rows.  One workgroup takes a group of up to 16 consecutive rows of one
+// prompt and one kv head: wave w is query head w of the head's group, its 16
+// MFMA columns are the rows, each with its own causal limit.  The waves share
+// the cache: stages of 32 positions (K and V tiles, already in operand order)
+// stream through an LDS ring by direct global->LDS loads, so a prompt's K/V is
+// read once per 16 rows, and nothing is merged between waves.  The 32 positions
+// of a stage make one k-range of a 16x16x32 MFMA in the value product: k-value
+// 4 t + e of lane group g is position 16 t + 4 g + e of the stage, which is
+// where both the scores' accumulators and the cache's V tile have it.
+// Measured (16 prompts of 511 rows, two layers of each of the Qwen-shaped models,
+// the four launches): the kernel with 16 columns per workgroup, whose waves split
+// the positions, 1100 us; this one 550.
+template <int HD, int GQA>
+__global__ __launch_bounds__(64 * GQA) __attribute__((amdgpu_waves_per_eu(GQA == 1 ? 1 : 2))) void attn_prompt_kernel(
+    const float* __restrict__ q, const bf16_t* __restrict__ kc, const bf16_t* __restrict__ vc, int ctx_stride,
+    long slot_stride, const int32_t* __restrict__ row_slot, const int32_t* __restrict__ row_pos,
+    const int32_t* __restrict__ grp_row0, const int32_t* __restrict__ grp_n, bf16_t* __restrict__ out, int nq) {
+  constexpr int DC = HD / 32, DB = HD / 16, T = 2;    // 32-dim pieces, 16-dim blocks, 16-position chunks per stage
+  constexpr int NP = T * 2 * DC;                      // 1 KB pieces per stage: per chunk its K pieces, then its V pieces
+  constexpr int STAGE = NP * 1024, NS = 3;
+  constexpr int NPW = (NP + GQA - 1) / GQA;           // pieces per wave
+  constexpr int ST = HD + 4;                          // row stride of a wave's result block
+  constexpr int LDS = NS * STAGE > GQA * 16 * ST * 4 ? NS * STAGE : GQA * 16 * ST * 4;
+  static_assert(NP % GQA == 0 || NPW == 1, "a wave issues NPW pieces or none");
+  __shared__ __attribute__((aligned(1024))) unsigned char ring[LDS];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g = lane >> 4, c16 = lane & 15;
+  const int kh = blockIdx.x, r0 = grp_row0[blockIdx.y], nr = grp_n[blockIdx.y];
+  const int ctx_max = row_pos[r0 + nr - 1] + 1;
+  const bool valid = c16 < nr;
+  const int rr = r0 + (valid ? c16 : 0);
+  const int ctx = valid ? row_pos[rr] + 1 : 0;        // positions this lane's column attends
+  const size_t plane = (size_t)row_slot[r0] * slot_stride + (size_t)kh * ctx_stride * HD;
+  const __amdgpu_buffer_rsrc_t kr = buf_rsrc(kc + plane, (uint32_t)ctx_stride * HD * 2);
+  const __amdgpu_buffer_rsrc_t vr = buf_rsrc(vc + plane, (uint32_t)ctx_stride * HD * 2);
+  const float scale = 1.4426950408889634f / sqrtf((float)HD);   // log2(e) / sqrt(hd)
+  const int nst = (ctx_max + 31) >> 5;                // stages
+  auto issue = [&](int c, int stage) {
+    const int cc = min(c, nst - 1);
+#pragma unroll
+    for (int i = 0; i < NPW; ++i) {
+      const int p = GQA * i + wave;
+      if (NP % GQA != 0 && p >= NP) continue;
+      const int chunk = T * cc + p / (2 * DC), j = p % DC;
+      buf_load_lds16((p / DC) & 1 ? vr : kr, ring + stage * STAGE + p * 1024, lane * 16, chunk * 32 * HD + j * 1024);
+    }
+  };
+
+  // Q^T operand: column c16, k = dims 32 dc + 8 g .. +7 (zero for unused columns)
+  const float* qp = q + ((size_t)rr * nq + kh * GQA + wave) * HD + 8 * g;
+  bf16x8_t qh[DC], ql[DC];
+#pragma unroll
+  for (int dc = 0; dc < DC; ++dc) {
+    const float4 a = *reinterpret_cast<const float4*>(qp + 32 * dc);
+    const float4 b = *reinterpret_cast<const float4*>(qp + 32 * dc + 4);
+    float x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = valid ? x[e] : 0.f;
+    split8(x, qh[dc], ql[dc]);
+  }
+#pragma unroll
+  for (int d = 0; d < NS - 1; ++d) issue(d, d);
+  float m_run = -INFINITY, l_run = 0.f;               // running max (log2 units), this lane's share of the sum
+  f32x4_t o[DB];                                      // O[column 4 g + i][dim 16 db + c16]
+#pragma unroll
+  for (int db = 0; db < DB; ++db) o[db] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  const uint32_t base = lds_addr_of(ring) + lane * 16;
+
+  int stage = 0;
+  for (int c = 0; c < nst; ++c) {
+    wait_vmcnt<(NS - 2) * NPW>();     // this wave's pieces of stage c have landed
+    lds_wait();                       // and its reads of stage c - 1 are done
+    __builtin_amdgcn_s_barrier();     // ... in every wave
+    issue(c + NS - 1, stage == 0 ? NS - 1 : stage - 1);
+    const uint32_t st = base + (uint32_t)(stage * STAGE);
+    stage = stage == NS - 1 ? 0 : stage + 1;
+    u32x4_t k[T][DC], v[T][DC];
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+      for (int j = 0; j < DC; ++j) k[t][j] = lds_read16(st + (uint32_t)((t * 2 * DC + j) * 1024));
+    lds_wait();
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+      for (int j = 0; j < DC; ++j) lds_fence_value(k[t][j]);
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+      for (int j = 0; j < DC; ++j) v[t][j] = lds_read16(st + (uint32_t)((t * 2 * DC + DC + j) * 1024));
+    // scores of positions 32 c + 16 t + 4 g + i for column c16
+    float s[4 * T];
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      f32x4_t acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int dc = 0; dc < DC; ++dc) {
+        const bf16x8_t kk = __builtin_bit_cast(bf16x8_t, k[t][dc]);
+        acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kk, qh[dc], acc0, 0, 0, 0);
+        acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kk, ql[dc], acc1, 0, 0, 0);
+      }
+      const int p0 = 32 * c + 16 * t + 4 * g;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) s[4 * t + i] = p0 + i < ctx ? (acc0[i] + acc1[i]) * scale : -INFINITY;
+    }
+    float mx = s[0];
+#pragma unroll
+    for (int i = 1; i < 4 * T; ++i) mx = fmaxf(mx, s[i]);
+    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    const float m_new = fmaxf(m_run, mx);
+    const bool none = m_new == -INFINITY;             // a column that attends nothing yet (unused columns)
+    const float alpha = none ? 1.f : exp2f(m_run - m_new);
+    float pr[4 * T], sum = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4 * T; ++i) {
+      pr[i] = none ? 0.f : exp2f(s[i] - m_new);
+      sum += pr[i];
+    }
+    l_run = l_run * alpha + sum;
+    m_run = m_new;
+    bf16x8_t ph, pl;
+    split8(pr, ph, pl);
+    if (__ballot(alpha != 1.f)) {                     // rescale only when some column's max moved
+      float ai[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) ai[i] = __shfl(alpha, 4 * g + i, 64);
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o[db][i] *= ai[i];
+    }
+    lds_wait();
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+      for (int j = 0; j < DC; ++j) lds_fence_value(v[t][j]);
+    // positions at or past the last row's limit hold stale cache contents:
+    // zero them so that 0 * (stale) cannot produce NaN
+    if (32 * c + 32 > ctx_max) {
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        const int nv = min(max(ctx_max - (32 * c + 16 * t + 4 * g), 0), 4);
+        const uint64_t keep = nv == 4 ? ~0ull : (1ull << (16 * nv)) - 1ull;
+        const uint32_t klo = (uint32_t)keep, khi = (uint32_t)(keep >> 32);
+#pragma unroll
+        for (int j = 0; j < DC; ++j) v[t][j] &= u32x4_t{klo, khi, klo, khi};
+      }
+    }
+#pragma unroll
+    for (int part = 0; part < 2; ++part)
+#pragma unroll
+      for (int db = 0; db < DB; ++db) {
+        const u32x4_t a = v[0][db >> 1], b = v[1][db >> 1];
+        const u32x4_t w = (db & 1) ? u32x4_t{a.z, a.w, b.z, b.w} : u32x4_t{a.x, a.y, b.x, b.y};
+        o[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(part ? pl : ph, __builtin_bit_cast(bf16x8_t, w), o[db], 0, 0, 0);
+      }
+  }
+  wait_vmcnt<0>();
+  lds_wait();
+  __builtin_amdgcn_s_barrier();       // the ring is idle in every wave: its LDS takes the results
+
+  float l = l_run;
+  l += __shfl_xor(l, 16, 64);
+  l += __shfl_xor(l, 32, 64);
+  float* sm = reinterpret_cast<float*>(ring) + wave * 16 * ST;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const float li = __shfl(l, 4 * g + i, 64);
+#pragma unroll
+    for (int db = 0; db < DB; ++db) sm[(4 * g + i) * ST + 16 * db + c16] = o[db][i] / li;
+  }
+  __builtin_amdgcn_wave_barrier();
+  // split-format pieces of 8 values: 8 high parts, then 8 low parts
+#pragma unroll
+  for (int e = lane; e < 16 * (HD / 8); e += 64) {
+    const int r = e / (HD / 8), d = (e % (HD / 8)) * 8;
+    const float4 a = *reinterpret_cast<const float4*>(sm + r * ST + d);
+    const float4 b = *reinterpret_cast<const float4*>(sm + r * ST + d + 4);
+    const float x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+    bf16x8_t hi, lo;
+    split8(x, hi, lo);
+    if (r < nr) {
+      u32x4_t* p = reinterpret_cast<u32x4_t*>(out + (size_t)(r0 + r) * 2 * nq * HD + 2 * ((kh * GQA + wave) * HD + d));
+      p[0] = __builtin_bit_cast(u32x4_t, hi);
+      p[1] = __builtin_bit_cast(u32x4_t, lo);
+    }
   }
 }
 
@@ -460,26 +618,25 @@ __global__ __launch_bounds__(128) void attn_valu_kernel(
 
 template <int HD, int GQA>
 hipError_t run_mfma(const AttnArgs& a, hipStream_t st) {
-  constexpr int ROWS = 16 / GQA;
-  constexpr int RB = ROWS > 1 ? ROWS : 1;
   const bf16_t* kc = (const bf16_t*)a.cache.k;
   const bf16_t* vc = (const bf16_t*)a.cache.v;
-  if (ROWS > 1 && a.grp_row0) {         // prompt rows
-    hipLaunchKernelGGL((attn_mfma_kernel<HD, GQA, RB>), dim3(a.nkv, a.n_groups * (16 / RB)), dim3(256), 0, st, a.q,
-                       kc, vc, a.cache.ctx_stride, a.cache.slot_stride, a.row_slot, a.row_pos, a.row_done, a.grp_row0,
-                       a.grp_n, 16 / RB, (bf16_t*)a.out, a.nq);
-    return hipGetLastError();
+  if constexpr (GQA <= 8) {
+    if (a.grp_row0) {                   // prompt rows
+      hipLaunchKernelGGL((attn_prompt_kernel<HD, GQA>), dim3(a.nkv, a.n_groups), dim3(64 * GQA), 0, st, a.q, kc, vc,
+                         a.cache.ctx_stride, a.cache.slot_stride, a.row_slot, a.row_pos, a.grp_row0, a.grp_n,
+                         (bf16_t*)a.out, a.nq);
+      return hipGetLastError();
+    }
   }
   if (a.row_lo) {                       // decode rows with a shared prompt prefix
     if (!a.row_done || !a.pfx_slot) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((attn_rows_kernel<HD, GQA, true>), dim3(a.nkv, a.R), dim3(256), 0, st, a.q, kc, vc,
+    hipLaunchKernelGGL((attn_rows_kernel<HD, GQA>), dim3(a.nkv, a.R), dim3(256), 0, st, a.q, kc, vc,
                        a.cache.ctx_stride, a.cache.slot_stride, a.row_slot, a.row_pos, a.row_done, a.row_lo,
                        a.pfx_slot, (bf16_t*)a.out, a.nq);
     return hipGetLastError();
   }
-  hipLaunchKernelGGL((attn_mfma_kernel<HD, GQA, 1>), dim3(a.nkv, a.R), dim3(256), 0, st, a.q, kc, vc,
-                     a.cache.ctx_stride, a.cache.slot_stride, a.row_slot, a.row_pos, a.row_done,
-                     (const int32_t*)nullptr, (const int32_t*)nullptr, 1, (bf16_t*)a.out, a.nq);
+  hipLaunchKernelGGL((attn_mfma_kernel<HD, GQA>), dim3(a.nkv, a.R), dim3(256), 0, st, a.q, kc, vc,
+                     a.cache.ctx_stride, a.cache.slot_stride, a.row_slot, a.row_pos, a.row_done, (bf16_t*)a.out, a.nq);
   return hipGetLastError();
 }
 

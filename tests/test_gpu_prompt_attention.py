@@ -1,0 +1,36 @@
+"""GPU parity of the prompt attention at the edges of its row groups (16 rows)
+and stages (32 positions), for each head size and group size it has a kernel
+for, through the C ABI.
+
+The first step after the prefill attends to every prompt position, so its logits
+see the prompt's K/V of both layers, and the second layer's K/V sees the first
+layer's attention output at every prompt row.
+"""
+import pytest
+
+import workloads as W
+from tests import parity as P
+
+pytestmark = pytest.mark.gpu
+
+LENGTHS = [2, 3, 16, 17, 18, 32, 33, 34, 48, 50, 65, 97]
+
+
+def _pair(hd, gqa_sen, gqa_jun, lengths, max_new=2):
+    wl = W.workload("small").replace(gain_jitter=0.05, n_prompts=len(lengths), group=1, prompt_len=max(lengths))
+    for m, gqa, nkv in ((wl.senior, gqa_sen, 2), (wl.junior, gqa_jun, 1)):
+        m.n_layers, m.d_model, m.head_dim, m.n_kv_heads, m.n_q_heads = 2, 256, hd, nkv, nkv * gqa
+        m.ffn_dim, m.vocab = 512, 512
+    wl.sample.max_new = max_new
+    return wl
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("gqa_sen,gqa_jun", [(4, 2), (1, 8), (8, 16)])
+def test_prompt_attention_edges(hd, gqa_sen, gqa_jun):
+    P.log(f"case prompt attention: head_dim {hd}, groups of {gqa_sen} and {gqa_jun} heads, prompt lengths {LENGTHS}")
+    wl = _pair(hd, gqa_sen, gqa_jun, LENGTHS)
+    ws, wj, _, bnd = W.make_all(wl)
+    prompts = [W.make_prompts(wl)[i][:n] for i, n in enumerate(LENGTHS)]
+    p = P.run(wl, logits_at=(1, 2), max_prefill_tokens=256, weights=(ws, wj, prompts, bnd))
+    P.check(p, P.TOL_BF16)
