@@ -228,6 +228,94 @@ __global__ __launch_bounds__(kNT) void qkv_post_kernel(
   }
 }
 
+// The same for prompt rows of a bf16 model: one wave per (group of up to 16
+// rows, head).  A group is one 16-position chunk of its prompt's cache, so the
+// keys and values are put in cache order in LDS and leave as whole 1 KB pieces
+// instead of 2-byte stores at a 16-byte stride, and a wave has the loads of
+// eight rows in flight (four for head_dim 128) instead of one.  Positions of
+// the chunk past the group's last row are written as zeros; no row attends
+// them before a decode step has written them.  Measured beside the other
+// model's forward (8176 rows, Qwen-shaped senior; 4056 rows, small senior): one
+// row and head per wave 232 and 35 us, this kernel 103 and 13 us.
+template <int HD>
+__global__ __launch_bounds__(kNT) void qkv_prompt_kernel(
+    const float* __restrict__ ws, int S, long ws_stride, int nq, int nkv, const float* __restrict__ q_norm,
+    const float* __restrict__ k_norm, float eps, const float2* __restrict__ rope,
+    const int32_t* __restrict__ row_slot, const int32_t* __restrict__ row_pos,
+    const int32_t* __restrict__ grp_row0, const int32_t* __restrict__ grp_n, float* __restrict__ q_out,
+    bf16_t* __restrict__ kc, bf16_t* __restrict__ vc, int ctx_stride, long slot_stride) {
+  constexpr int HALF = HD / 2, RPW = 64 / HALF;      // lane i of a row's HALF lanes has dims i and i + HALF
+  constexpr int ITER = 16 / RPW, U = 4;
+  __shared__ __attribute__((aligned(16))) bf16_t tiles[kNT / 64][16 * HD];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int nh = nq + 2 * nkv, head = blockIdx.y * (kNT / 64) + wave;
+  if (head >= nh) return;
+  const int r0 = grp_row0[blockIdx.x], n = grp_n[blockIdx.x];
+  const int sub = lane / HALF, l = lane % HALF;
+  const int pos0 = row_pos[r0];
+  const bool isq = head < nq, isv = head >= nq + nkv;
+  const float* gn = isq ? q_norm : k_norm;
+  bf16_t* tile = tiles[wave];
+#pragma unroll
+  for (int it0 = 0; it0 < ITER; it0 += U) {
+    float x1[U], x2[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) x1[u] = x2[u] = 0.f;
+    for (int s = 0; s < S; ++s) {
+      float a1[U], a2[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int i = (it0 + u) * RPW + sub;
+        const float* p = ws + s * ws_stride + ((size_t)(r0 + min(i, n - 1)) * nh + head) * HD + l;
+        a1[u] = p[0];
+        a2[u] = p[HALF];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        x1[u] += a1[u];
+        x2[u] += a2[u];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = (it0 + u) * RPW + sub;            // row of the group = position in the chunk
+      float y1 = x1[u], y2 = x2[u];
+      if (!isv) {
+        if (gn) {
+          float ss = y1 * y1 + y2 * y2;
+#pragma unroll
+          for (int o = HALF / 2; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
+          const float rs = 1.f / sqrtf(ss / (float)HD + eps);
+          y1 *= rs * gn[l];
+          y2 *= rs * gn[l + HALF];
+        }
+        const float2 cs = rope[(size_t)(pos0 + min(i, n - 1)) * HALF + l];
+        const float z1 = y1 * cs.x - y2 * cs.y, z2 = y2 * cs.x + y1 * cs.y;
+        y1 = z1;
+        y2 = z2;
+      }
+      if (isq) {
+        if (i < n) {
+          float* qo = q_out + ((size_t)(r0 + i) * nq + head) * HD;
+          qo[l] = y1;
+          qo[l + HALF] = y2;
+        }
+      } else {
+        if (i >= n) y1 = y2 = 0.f;
+        tile[isv ? kv_v_index(i, l, HD) : kv_k_index(i, l, HD)] = f2bf(y1);
+        tile[isv ? kv_v_index(i, l + HALF, HD) : kv_k_index(i, l + HALF, HD)] = f2bf(y2);
+      }
+    }
+  }
+  if (isq) return;
+  __builtin_amdgcn_wave_barrier();
+  const int kh = isv ? head - nq - nkv : head - nq;
+  bf16_t* dst = (isv ? vc : kc) + (size_t)row_slot[r0] * slot_stride + (size_t)kh * ctx_stride * HD + (size_t)pos0 * HD;
+#pragma unroll
+  for (int e = 0; e < 16 * HD / 8; e += 64)
+    if (e + lane < 16 * HD / 8) reinterpret_cast<uint4*>(dst)[e + lane] = reinterpret_cast<const uint4*>(tile)[e + lane];
+}
+
 __global__ void rope_table_kernel(double theta, int hd, int n_pos, float2* __restrict__ out) {
   const int half = hd / 2;
   const long n = (long)n_pos * half;
@@ -607,24 +695,25 @@ __global__ __launch_bounds__(64) void sample_finish_kernel(FinishArgs a) {
 }
 
 // ----------------------------------------------------- replication / state
+// Positions [p0, P - 1) of prompt j = j0 + blockIdx.z from the slot of its
+// first sequence to the slot of sequence 1 + blockIdx.y of its group, p0 = P - 1
+// rounded down to 16 where the rest is shared, else 0: whole 16-position chunks,
+// a contiguous range of each tiled plane (every prompt of a chunk in one launch;
+// a launch per prompt and model took 5 us each).
 template <typename T>
 __global__ __launch_bounds__(kNT) void kv_replicate_kernel(T* kc, T* vc, int nkv, int hd, int ctx_stride,
-                                                           long layer_stride, long slot_stride, int src,
-                                                           int dst0, int p0, int n_pos) {
-  const int lk = blockIdx.x;                 // layer * nkv + kv head
-  const int layer = lk / nkv, kh = lk % nkv;
-  const int dst = dst0 + blockIdx.y;
-  const size_t kh_off = (size_t)kh * ctx_stride * hd;
-  // positions p0 .. n_pos-1 (p0 a multiple of 16) occupy the whole
-  // 16-position chunks that hold them: a contiguous range of each tiled plane
-  const long e0 = (long)p0 * hd;
-  const long n = (long)((n_pos + 15) >> 4) * 16 * hd;
-  const T* ks = kc + layer * layer_stride + (size_t)src * slot_stride + kh_off;
-  T* kd = kc + layer * layer_stride + (size_t)dst * slot_stride + kh_off;
-  for (long e = e0 + threadIdx.x; e < n; e += kNT) kd[e] = ks[e];
-  const T* vs = vc + layer * layer_stride + (size_t)src * slot_stride + kh_off;
-  T* vd = vc + layer * layer_stride + (size_t)dst * slot_stride + kh_off;
-  for (long e = e0 + threadIdx.x; e < n; e += kNT) vd[e] = vs[e];
+                                                           long layer_stride, long slot_stride, int j0, int G,
+                                                           const int32_t* __restrict__ prompt_len, int share) {
+  const int j = j0 + blockIdx.z, n_pos = prompt_len[j] - 1;
+  const long c0 = share ? n_pos >> 4 : 0, c1 = (n_pos + 15) >> 4;
+  const int layer = blockIdx.x / nkv, kh = blockIdx.x % nkv;
+  const size_t src = layer * layer_stride + (size_t)(j * G) * slot_stride + (size_t)kh * ctx_stride * hd;
+  const size_t dst = src + (size_t)(1 + blockIdx.y) * slot_stride;
+  constexpr int V = 16 / sizeof(T);                  // a chunk is a multiple of 1 KB
+  for (long e = c0 * 16 * hd / V + threadIdx.x; e < c1 * 16 * hd / V; e += kNT) {
+    reinterpret_cast<uint4*>(kc + dst)[e] = reinterpret_cast<const uint4*>(kc + src)[e];
+    reinterpret_cast<uint4*>(vc + dst)[e] = reinterpret_cast<const uint4*>(vc + src)[e];
+  }
 }
 
 __global__ void init_state_kernel(InitStateArgs a) {
@@ -815,7 +904,22 @@ hipError_t launch_resid_norm(int dt, const float* ws, int S, long ws_stride, flo
 hipError_t launch_qkv_post(const QkvPostArgs& a, hipStream_t st) {
   if (a.R <= 0) return hipSuccess;
   if (a.S > kSplitMaxDev || a.hd > 128) return hipErrorInvalidValue;
-  const dim3 grid(a.R, (a.nq + 2 * a.nkv + kNT / 64 - 1) / (kNT / 64));
+  const int hb = (a.nq + 2 * a.nkv + kNT / 64 - 1) / (kNT / 64);
+  if (a.dt == DT_BF16 && a.grp_row0) {               // prompt rows in groups of one cache chunk
+    auto run = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(a.n_groups, hb), dim3(kNT), 0, st, a.ws, a.S, a.ws_stride, a.nq, a.nkv, a.q_norm,
+                         a.k_norm, a.eps, a.rope, a.row_slot, a.row_pos, a.grp_row0, a.grp_n, a.q_out,
+                         (bf16_t*)a.cache.k, (bf16_t*)a.cache.v, a.cache.ctx_stride, a.cache.slot_stride);
+      return hipGetLastError();
+    };
+    switch (a.hd) {
+      case 32: return run(qkv_prompt_kernel<32>);
+      case 64: return run(qkv_prompt_kernel<64>);
+      case 128: return run(qkv_prompt_kernel<128>);
+      default: return hipErrorInvalidValue;
+    }
+  }
+  const dim3 grid(a.R, hb);
   if (a.dt == DT_BF16)
     hipLaunchKernelGGL((qkv_post_kernel<bf16_t>), grid, dim3(kNT), 0, st, a.ws, a.S, a.ws_stride,
                        a.nq, a.nkv, a.hd, a.q_norm, a.k_norm, a.eps, a.rope, a.row_slot, a.row_pos,
@@ -856,18 +960,19 @@ hipError_t launch_sample_finish(const FinishArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_kv_replicate(int dt, void* kc, void* vc, int n_layers, long layer_stride,
-                               long slot_stride, int nkv, int hd, int ctx_stride, int src,
-                               int dst0, int n_dst, int p0, int n_pos, hipStream_t st) {
-  if (n_dst <= 0 || n_pos <= p0) return hipSuccess;
-  if (p0 < 0 || p0 % 16 || n_pos > ctx_stride) return hipErrorInvalidValue;
-  dim3 grid(n_layers * nkv, n_dst);
-  if (dt == DT_BF16)
-    hipLaunchKernelGGL((kv_replicate_kernel<bf16_t>), grid, dim3(kNT), 0, st, (bf16_t*)kc, (bf16_t*)vc,
-                       nkv, hd, ctx_stride, layer_stride, slot_stride, src, dst0, p0, n_pos);
-  else
-    hipLaunchKernelGGL((kv_replicate_kernel<float>), grid, dim3(kNT), 0, st, (float*)kc, (float*)vc,
-                       nkv, hd, ctx_stride, layer_stride, slot_stride, src, dst0, p0, n_pos);
+hipError_t launch_kv_replicate(int dt, void* kc, void* vc, int n_layers, long layer_stride, long slot_stride, int nkv,
+                               int hd, int ctx_stride, int j0, int n_prompts, int G, const int32_t* prompt_len,
+                               bool share, hipStream_t st) {
+  if (G <= 1) return hipSuccess;
+  for (int j = 0; j < n_prompts; j += 65535) {       // grid.z limit
+    const dim3 grid(n_layers * nkv, G - 1, std::min(n_prompts - j, 65535));
+    if (dt == DT_BF16)
+      hipLaunchKernelGGL((kv_replicate_kernel<bf16_t>), grid, dim3(kNT), 0, st, (bf16_t*)kc, (bf16_t*)vc, nkv, hd,
+                         ctx_stride, layer_stride, slot_stride, j0 + j, G, prompt_len, share ? 1 : 0);
+    else
+      hipLaunchKernelGGL((kv_replicate_kernel<float>), grid, dim3(kNT), 0, st, (float*)kc, (float*)vc, nkv, hd,
+                         ctx_stride, layer_stride, slot_stride, j0 + j, G, prompt_len, share ? 1 : 0);
+  }
   return hipGetLastError();
 }
 

@@ -136,6 +136,9 @@ struct QkvPostArgs {
   const int32_t* row_slot; const int32_t* row_pos; const int32_t* row_done;
   float* q_out;           // [R][nq][hd]
   CacheGeom cache;
+  // prompt rows: n_groups groups of at most 16 consecutive rows of one prompt
+  // (one 16-position chunk each); NULL at decode
+  const int32_t* grp_row0; const int32_t* grp_n; int n_groups;
 };
 hipError_t launch_qkv_post(const QkvPostArgs& a, hipStream_t st);
 
@@ -243,11 +246,13 @@ hipError_t launch_grpo(const GrpoArgs& a, hipStream_t st);
 constexpr size_t kGrpoStaticBytes = (size_t)1 << 20;
 hipError_t grpo_static_workspace(void** ptr);
 
-// Copy positions [p0, n_pos) of slot src into slots dst0 .. dst0 + n_dst - 1
-// for every layer and kv head (K and transposed V); p0 % 16 == 0.
-hipError_t launch_kv_replicate(int dt, void* kc, void* vc, int n_layers, long layer_stride,
-                               long slot_stride, int nkv, int hd, int ctx_stride, int src,
-                               int dst0, int n_dst, int p0, int n_pos, hipStream_t st);
+// Copy the last partial chunk (share) or all prompt positions (else) of prompts
+// j0 .. j0 + n_prompts - 1 from the slot of each prompt's first sequence (j G)
+// into those of its other G - 1 sequences, for every layer and kv head (K and
+// V).
+hipError_t launch_kv_replicate(int dt, void* kc, void* vc, int n_layers, long layer_stride, long slot_stride, int nkv,
+                               int hd, int ctx_stride, int j0, int n_prompts, int G, const int32_t* prompt_len,
+                               bool share, hipStream_t st);
 
 // Per-sequence state after prefill.  The pending token (a prompt's last
 // token) is range-checked like the prompt rows (see PrefillRowsArgs).

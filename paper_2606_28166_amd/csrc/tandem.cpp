@@ -548,6 +548,7 @@ tandem_status forward_layer(tandem_handle* h, Model& m, int l, const FwdRows& fr
     qp.eps = c.rms_eps; qp.rope = m.rope;
     qp.row_slot = fr.slot; qp.row_pos = fr.pos; qp.row_done = fr.done;
     qp.q_out = m.q; qp.cache = cg;
+    qp.grp_row0 = fr.grp_row0; qp.grp_n = fr.grp_n; qp.n_groups = fr.n_groups;
     TIMED(TANDEM_K_OTHER, launch_qkv_post(qp, st));
   }
 
@@ -1217,15 +1218,12 @@ tandem_status tandem_prefill(tandem_handle* h, const int32_t* prompt_tokens, con
       tandem_status s = forward_pair(h, fr, false);
       if (s != TANDEM_OK) return s;
     }
-    for (int j = j0; j < j1; ++j) {
-      const int P = prompt_offsets[j + 1] - prompt_offsets[j];
-      if (P - 1 <= 0 || G <= 1) continue;
-      const int lo = share ? (P - 1) / 16 * 16 : 0;    // shared positions stay in the first slot only
+    if (G > 1) {                        // shared positions stay in the first slot only
       for (int i = 0; i < h->nm; ++i) {
         Model& m = h->m[i];
         TIMED(TANDEM_K_OTHER, launch_kv_replicate(m.cfg.weight_dtype == TANDEM_BF16 ? DT_BF16 : DT_F32, m.kc, m.vc,
                                    m.cfg.n_layers, m.layer_stride, m.slot_stride, m.cfg.n_kv_heads,
-                                   m.cfg.head_dim, h->plan.ctx_stride, j * G, j * G + 1, G - 1, lo, P - 1, st));
+                                   m.cfg.head_dim, h->plan.ctx_stride, j0, j1 - j0, G, h->p_len, share, st));
       }
     }
   }
