@@ -227,17 +227,18 @@ struct ScoreArgs {
 hipError_t launch_score(const ScoreArgs& a, hipStream_t st);
 
 // Senior-only GRPO loss pieces over S = n_groups * G rollouts with arenas of
-// row stride T: advantages adv[S], masked counts cnt[S] (scratch), per-(row,
-// chunk) partial sums part[S][n_chunks] (scratch, n_chunks = ceil(T /
-// kGrpoChunk)), a completion ticket (scratch, zeroed by the first launch),
-// gradient grad[S][T] (may be NULL), loss[1], n_masked[1].
-// logp_new NULL means logp_new = logp_old.
+// row stride T: advantages adv[S], masked counts cnt[S] (scratch), per-row sums
+// part[S] and what their rounding left out part_lo[S] (scratch; part_lo NULL where
+// there is no room: rows of one chunk), gradient grad[S][T] (may be NULL),
+// loss[1], n_masked[1].
+// logp_new NULL means logp_new = logp_old.  kGrpoChunk enters the size of the
+// workspace only, which the entry points keep as callers know it.
 constexpr int kGrpoChunk = 1024;
 struct GrpoArgs {
-  int S, G, T, n_chunks; float eps;
+  int S, G, T; float eps;
   const float* rewards; const uint8_t* owner; const int32_t* length;
   const float* logp_old; const float* logp_new;
-  float* adv; int32_t* cnt; float* part; int32_t* ticket; float* grad; float* loss; int32_t* n_masked;
+  float* adv; int32_t* cnt; float* part; float* part_lo; float* grad; float* loss; int32_t* n_masked;
 };
 hipError_t launch_grpo(const GrpoArgs& a, hipStream_t st);
 // Bytes of the device-resident workspace of the allocation-free GRPO entry

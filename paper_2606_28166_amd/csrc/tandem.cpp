@@ -876,10 +876,11 @@ tandem_status grpo_check(const tandem_grpo_cfg* c, size_t* bytes, GrpoArgs* a) {
   if (!(c->clip_eps >= 0.f && c->clip_eps < 1.f))
     return fail(nullptr, TANDEM_E_ARG, "tandem_grpo: clip_eps must lie in [0, 1)");
   a->S = (int)S; a->G = c->group_size; a->T = c->max_new_tokens; a->eps = c->clip_eps;
-  a->n_chunks = (a->T + kGrpoChunk - 1) / kGrpoChunk;
-  // counts [S] int32, partial sums [S][n_chunks] float, a ticket int32, each 256-aligned
+  // counts [S] int32, sums and their remainders [S] float, 256-aligned; the size asked for is the one of sums by
+  // kGrpoChunk positions and one more counter, so that what fits a workspace of a known size stays what it was
   const size_t cnt_b = ((size_t)S * 4 + 255) / 256 * 256;
-  *bytes = cnt_b + ((size_t)S * a->n_chunks * 4 + 255) / 256 * 256 + 256;
+  const size_t n_chunks = (size_t)(a->T + kGrpoChunk - 1) / kGrpoChunk;
+  *bytes = cnt_b + ((size_t)S * n_chunks * 4 + 255) / 256 * 256 + 256;
   return TANDEM_OK;
 }
 }  // namespace
@@ -1366,7 +1367,7 @@ tandem_status tandem_grpo_loss(const tandem_grpo_cfg* cfg, const float* rewards,
   a.adv = advantages; a.grad = grad; a.loss = loss; a.n_masked = n_masked;
   a.cnt = static_cast<int32_t*>(workspace);
   a.part = reinterpret_cast<float*>(static_cast<char*>(workspace) + ((size_t)a.S * 4 + 255) / 256 * 256);
-  a.ticket = reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + need - 256);
+  a.part_lo = a.T > kGrpoChunk ? a.part + a.S : nullptr;   // the second of two or more floats per row
   const hipError_t e = launch_grpo(a, static_cast<hipStream_t>(stream));
   if (e != hipSuccess)
     return fail(nullptr, TANDEM_E_HIP, std::string("tandem_grpo_loss: ") + hipGetErrorString(e));
@@ -1400,7 +1401,7 @@ tandem_status tandem_grpo_loss_noalloc(const tandem_grpo_cfg* cfg, const float* 
   a.adv = advantages; a.grad = grad; a.loss = loss; a.n_masked = n_masked;
   a.cnt = static_cast<int32_t*>(ws);
   a.part = reinterpret_cast<float*>(static_cast<char*>(ws) + ((size_t)a.S * 4 + 255) / 256 * 256);
-  a.ticket = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + need - 256);
+  a.part_lo = a.T > kGrpoChunk ? a.part + a.S : nullptr;   // the second of two or more floats per row
   e = launch_grpo(a, static_cast<hipStream_t>(stream));
   if (e != hipSuccess)
     return fail(nullptr, TANDEM_E_HIP, std::string("tandem_grpo_loss_noalloc: ") + hipGetErrorString(e));

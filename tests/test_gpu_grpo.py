@@ -68,6 +68,17 @@ def test_grpo_loss_matches_oracle(n_groups, G, T):
     P.log(f"  loss {got['loss'][0]:.6f}, {got['n_masked'][0]} masked positions, {edges} at a clip edge")
 
 
+@pytest.mark.parametrize("n_groups,G,T", [(1, 1, 1), (2, 3, 3), (1, 70, 1023), (2, 5, 1025), (1, 4, 4095), (2, 2, 4097),
+                                          (1, 3, 9001)])
+def test_grpo_row_passes(n_groups, G, T):
+    """Rows of one position, of a last quad that is not full, of one pass and of
+    several of either workgroup size, and a group of more rewards than a wave has
+    lanes; the bar is that of the other batches."""
+    P.log(f"case grpo row passes {n_groups}x{G} rollouts, stride {T}")
+    batch = W.make_grpo_batch(n_groups, G, T, seed=5 + T)
+    _check(_gpu(*batch, G), *batch, G)
+
+
 def test_grpo_ratio_one_no_gradient_and_empty_mask():
     """logp_new = NULL (the first update of a GRPO step, where the policy is
     still pi_old: every ratio is 1) without a gradient buffer; then an
