@@ -581,11 +581,15 @@ __global__ __launch_bounds__(128) void attn_valu_kernel(
   __syncthreads();
   const float scale = 1.f / sqrtf((float)hd);
   float m_run = -INFINITY, l_run = 0.f, o = 0.f;
+  // the value product: thread (part, dim) takes positions part, part + parts, ..
+  // of a block, several loads in flight
+  const int parts = 128 / hd, part = tid / hd, dim = tid % hd;
   for (int p0 = 0; p0 < ctx; p0 += 128) {
     const int p = p0 + tid;
     float s = -INFINITY;
     if (p < ctx) {
       float acc = 0.f;
+#pragma unroll 16
       for (int d = 0; d < hd; ++d) acc += sq[d] * ld(kbase + kv_k_index(p, d, hd));
       s = acc * scale;
     }
@@ -604,16 +608,23 @@ __global__ __launch_bounds__(128) void attn_valu_kernel(
     __syncthreads();
     ls = red[0] + red[1];
     l_run = l_run * alpha + ls;
-    if (tid < hd) {
+    if (part < parts) {
       const int n = min(128, ctx - p0);
       float acc = 0.f;
-      for (int t = 0; t < n; ++t) acc += sp[t] * ld(vbase + kv_v_index(p0 + t, tid, hd));
+#pragma unroll 8
+      for (int t = part; t < n; t += parts) acc += sp[t] * ld(vbase + kv_v_index(p0 + t, dim, hd));
       o = o * alpha + acc;
     }
     m_run = m_new;
     __syncthreads();
   }
-  if (tid < hd) act_store<SPLIT>(out, r, width, h * hd + tid, o / l_run);
+  sp[tid] = o;
+  __syncthreads();
+  if (tid < hd) {
+    float sum = 0.f;
+    for (int i = 0; i < parts; ++i) sum += sp[i * hd + tid];
+    act_store<SPLIT>(out, r, width, h * hd + tid, sum / l_run);
+  }
 }
 
 template <int HD, int GQA>

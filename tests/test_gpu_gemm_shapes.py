@@ -42,3 +42,17 @@ def test_projection_tile_edges(n_prompts, group, prompt_len, vocab, rows):
     p = P.run(_small(n_prompts, group, prompt_len, vocab), logits_at=(1, 2), seq_subset=rows)
     P.check(p, P.TOL_BF16)
     assert np.isfinite(p.out["logprob"]).all()
+
+
+# the float32 pair: up to 32 rows on the few-row kernel (4 or 8 rows at a time),
+# above it the 32 x 32 tiles; 1023 and 511 are vocabularies with a last odd column
+@pytest.mark.parametrize("n_prompts,group,prompt_len,vocab", [
+    (1, 1, 2, 512), (1, 4, 6, 511), (1, 5, 9, 512), (3, 3, 4, 1023), (1, 31, 33, 512), (2, 16, 17, 511),
+    (3, 11, 12, 512)])
+def test_float32_projections_of_few_rows(n_prompts, group, prompt_len, vocab):
+    P.log(f"case float32 GEMM shapes: {n_prompts} prompts of {prompt_len} tokens x {group}, V {vocab}")
+    wl = W.workload("tiny").replace(gain_jitter=0.1, n_prompts=n_prompts, group=group, prompt_len=prompt_len)
+    wl.senior.vocab = wl.junior.vocab = vocab
+    wl.sample.max_new = 3
+    p = P.run(wl, logits_at=(1, 3))
+    P.check(p, P.TOL_F32)
