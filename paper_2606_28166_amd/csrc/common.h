@@ -96,7 +96,9 @@ __device__ __forceinline__ void load_lds16_nt(const void* gsrc, void* lds_base) 
 }
 
 // 16 bytes per lane through a buffer descriptor straight into LDS at lds_base
-// + 16 * lane: per-lane and uniform byte offsets, zeros past the buffer's size.
+// + 16 * lane: per-lane and uniform byte offsets.  Lanes whose per-lane offset is
+// past the buffer's size read zeros; the uniform offset is not to be relied on
+// there (the range check may leave it out), so a caller keeps it inside.
 __device__ __forceinline__ void buf_load_lds16(__amdgpu_buffer_rsrc_t r, void* lds_base, int voff, int soff) {
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_t*)lds_base, 16, voff, soff, 0, 0);
 }
@@ -122,8 +124,9 @@ __device__ __forceinline__ int kv_v_index(int p, int d, int hd) {
   return (p >> 4) * 16 * hd + ((((d >> 5) * 64) + (j >> 2) * 16 + (d & 15)) << 3) + (((d >> 4) & 1) << 2) + (j & 3);
 }
 
-// Raw buffer access: a uniform base and a byte size (reads at or past the
-// size return zeros), per-lane 32-bit byte offsets, a uniform byte offset.
+// Raw buffer access: a uniform base and a byte size, per-lane 32-bit byte offsets
+// (lanes at or past the size read zeros) and a uniform byte offset, which callers
+// keep inside the size.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_rsrc(const void* base, uint32_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)bytes, 0x00020000);
 }

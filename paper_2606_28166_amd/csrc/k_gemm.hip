@@ -32,6 +32,7 @@
 
 #include "common.h"
 #include "kernels.h"
+#include "tile_plan.h"
 
 namespace tandem {
 
@@ -250,8 +251,9 @@ __global__ __launch_bounds__(64 * NWT) void gemm_mfma_kernel(
 // 64-wide chunk (M = 8176, us): senior QKV 466 -> 381 (1.35 PFLOP/s of MFMA),
 // O 333 -> 269, gate/up + SwiGLU 954 -> 721 (1.13 PFLOP/s), down 511 -> 423;
 // 1024 rows of the small senior: gate/up 32 -> 25.5, down 23 -> 15.2.
-// A 5-stage ring is no faster than 4 stages.  Rows past M and blocks past N
-// lie outside the buffer descriptors and read as zeros.
+// A 5-stage ring is no faster than 4 stages.  Rows past M lie outside the
+// activations' descriptor by their per-lane offset and read as zeros; blocks past
+// N repeat the last one.
 template <int BM_, int BN_, int WM_, int NS_, bool A16> struct TileShape {
   static constexpr int NW = 4;                        // waves
   static constexpr int BM = BM_, BN = BN_;
@@ -326,8 +328,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OCC))) void
     if (i < G::NA) {
       buf_load_lds16(ar, st + (NW * i + wave) * 1024, avoff[i], kc * G::RB);
     } else {
-      const int f = NW * (i - G::NA) + wave;              // fragment: block f / 2 of the tile, k-step f % 2
-      buf_load_lds16(wr, st + G::ASTAGE + f * 1024, lane * 16, ((f >> 1) * kfr + 2 * kc + (f & 1)) * 1024);
+      const int f = NW * (i - G::NA) + wave;
+      buf_load_lds16(wr, st + G::ASTAGE + f * 1024, lane * 16, tile_weight_offset(f, kc, kfr, nblk - b0));
     }
   };
   f32x16_t acc[MBW][NBW];
