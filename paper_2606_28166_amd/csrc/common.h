@@ -240,10 +240,10 @@ __device__ __forceinline__ Top2 merge_top2(Top2 A, Top2 B) {
   }
   return out;
 }
-// Running (max m, sum l of e^(v - m)) pairs merged.
+// Running (max m, sum l of e^(v - m)) pairs merged (a NaN sum stays).
 __device__ __forceinline__ void merge_lse(float& m, float& l, float m2, float l2) {
   const float M = fmaxf(m, m2);
-  if (M == -INFINITY) { m = M; l = 0.f; return; }
+  if (M == -INFINITY) { m = M; l += l2; return; }
   l = l * expf(m - M) + l2 * expf(m2 - M);
   m = M;
 }

@@ -354,14 +354,19 @@ __device__ __forceinline__ void store_quad(float* row, int v, int v1, const floa
       if (v + e < v1) row[v + e] = x[e];
   }
 }
-// (max, sum of e^(x - max)) of n values held in registers: one exponential each
+// (max, sum of e^(x - max)) of n values held in registers: one exponential each.
+// A NaN among them makes the sum NaN, also beside nothing but -inf.
 template <int N>
 __device__ __forceinline__ void lse_of(const float* x, float& m, float& l) {
   m = -INFINITY;
   l = 0.f;
 #pragma unroll
   for (int i = 0; i < N; ++i) m = fmaxf(m, x[i]);
-  if (m == -INFINITY) return;
+  if (m == -INFINITY) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) l += x[i] == -INFINITY ? 0.f : x[i];
+    return;
+  }
   float l0 = 0.f, l1 = 0.f;
 #pragma unroll
   for (int i = 0; i < N; i += 2) {

@@ -60,3 +60,26 @@ def test_sampling_and_scores_from_the_dumped_logits(vocab):
                 assert sampled[s] == int(np.argmax(g)), (t, s)
         forced = (forced + 3) % (vocab - 1)
     eng.close()
+
+
+# an entry alone in its thread's 16 (257), in its chunk (4097), and inside one (300: entry 256 of a full quad)
+@pytest.mark.parametrize("vocab,bad", [(257, 256), (4097, 4096), (300, 256)])
+def test_a_nan_logit_reaches_the_log_probs_and_scores(vocab, bad):
+    """A NaN in one row of both LM heads: the log-softmax and the scores of
+    every position are NaN, wherever the entry sits."""
+    from paper_2606_28166_amd.engine import TandemEngine
+    P.log(f"case NaN logit: entry {bad} of {vocab}")
+    wl = W.workload("tiny").replace(gain_jitter=0.1, n_prompts=2, group=2, prompt_len=5)
+    wl.senior.vocab = wl.junior.vocab = vocab
+    wl.sample = W.SampleSettings(0.7, -1, 0.0, 0.0, 2)
+    ws, wj, prompts, _ = W.make_all(wl)
+    for w in (ws, wj):
+        w["lm_head"][bad, 0] = np.nan
+    n = wl.n_seqs
+    eng = TandemEngine(wl.senior, ws, wl.junior, wj, wl.switch, wl.sample, wl.philox_seed, max_seqs=n, max_ctx=16)
+    eng.prefill(prompts, wl.group)
+    dbg = eng.step_forced(np.arange(n), logits=True)
+    assert np.isnan(dbg["logits_senior"][:n, bad].cpu().numpy()).all()
+    assert np.isnan(eng.score()[:n].cpu().numpy()).all()
+    assert np.isnan(eng.outputs()["logprob"][:, 0]).all()
+    eng.close()
