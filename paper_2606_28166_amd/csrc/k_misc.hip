@@ -408,18 +408,23 @@ __global__ __launch_bounds__(kNT) void sample_partials_kernel(SampleArgs a) {
   const int tt = a.t[s];
   // Scores of the senior, then those of the owner: (z + bias) / T, the
   // quotient from 1 / T with one correction step (the rounding of a division,
-  // in 3 operations instead of about 10; infinities and the padding as they are)
+  // in 3 operations instead of about 10; infinities and the padding as they are).
+  // A temperature whose reciprocal overflows (2^-128 and below) takes divisions.
   const float inv_t = 1.f / a.temp;
   auto over_t = [&](float z) {
     const float q = z * inv_t;
     return fabsf(q) < INFINITY ? fmaf(fmaf(-q, a.temp, z), inv_t, q) : q;
   };
+  auto scores = [&](auto&& quotient) {
 #pragma unroll
-  for (int i = 0; i < 4 * kVocabQuads; ++i) {
-    const int v = v0 + 4 * (kNT * (i >> 2) + tid) + (i & 3);
-    x[i] = over_t(x[i] + (v == a.eos_id ? a.eos_bias_sen : 0.f));
-    if (!own_sen) y[i] = over_t(y[i] + (v == a.eos_id ? a.eos_bias_jun : 0.f));
-  }
+    for (int i = 0; i < 4 * kVocabQuads; ++i) {
+      const int v = v0 + 4 * (kNT * (i >> 2) + tid) + (i & 3);
+      x[i] = quotient(x[i] + (v == a.eos_id ? a.eos_bias_sen : 0.f));
+      if (!own_sen) y[i] = quotient(y[i] + (v == a.eos_id ? a.eos_bias_jun : 0.f));
+    }
+  };
+  if (inv_t < INFINITY) scores(over_t);
+  else scores([&](float z) { return z / a.temp; });
   float ms, ls;
   lse_of<4 * kVocabQuads>(x, ms, ls);
   Top2 top{-INFINITY, 0x7FFFFFFF, -INFINITY};

@@ -83,3 +83,32 @@ def test_a_nan_logit_reaches_the_log_probs_and_scores(vocab, bad):
     assert np.isnan(eng.score()[:n].cpu().numpy()).all()
     assert np.isnan(eng.outputs()["logprob"][:, 0]).all()
     eng.close()
+
+
+def test_a_temperature_whose_reciprocal_overflows():
+    """T = 1e-39 (2^-128 and below: 1 / T is infinite in float32): scores z / T
+    of small logits, zero among them, are finite, and the largest one has all
+    the probability.  The bar is the rounding of z / T (2^-24 of scores of 1e37,
+    twice)."""
+    from paper_2606_28166_amd.engine import TandemEngine
+    P.log("case temperature 1e-39")
+    wl = W.workload("tiny").replace(gain_jitter=0.1, n_prompts=2, group=3, prompt_len=5)
+    wl.sample = W.SampleSettings(1e-39, -1, 0.0, 0.0, 2)
+    ws, wj, prompts, _ = W.make_all(wl)
+    for w in (ws, wj):
+        w["lm_head"] = w["lm_head"] * np.float32(0.05)
+        w["lm_head"][7] = 0                      # a logit of zero
+    n = wl.n_seqs
+    eng = TandemEngine(wl.senior, ws, wl.junior, wj, wl.switch, wl.sample, wl.philox_seed, max_seqs=n, max_ctx=16)
+    eng.prefill(prompts, wl.group)
+    own = eng.state()["owner"]
+    forced = np.array([7, 1, 2, 3, 7, 5])
+    dbg = eng.step_forced(forced, logits=True)
+    z = {k: dbg[f"logits_{k}"][:n].cpu().numpy().astype(np.float64) for k in ("senior", "junior")}
+    s = z["senior"] / np.float64(np.float32(1e-39))
+    assert np.abs(s).max() < 1e38
+    lp = s[np.arange(n), forced] - s.max(1)
+    np.testing.assert_allclose(eng.outputs()["logprob"][:, 0], lp, rtol=0, atol=np.abs(s).max() * 2.0 ** -22)
+    owner_z = np.where(own[:, None] != 0, z["senior"], z["junior"])
+    np.testing.assert_array_equal(dbg["sampled"][:n].cpu().numpy(), owner_z.argmax(1))
+    eng.close()
