@@ -228,15 +228,17 @@ __global__ __launch_bounds__(kNT) void qkv_post_kernel(
   }
 }
 
-// The same for prompt rows of a bf16 model: one wave per (group of up to 16
+// The same for many prompt rows of a bf16 model: one wave per (group of up to 16
 // rows, head).  A group is one 16-position chunk of its prompt's cache, so the
 // keys and values are put in cache order in LDS and leave as whole 1 KB pieces
 // instead of 2-byte stores at a 16-byte stride, and a wave has the loads of
 // eight rows in flight (four for head_dim 128) instead of one.  Positions of
 // the chunk past the group's last row are written as zeros; no row attends
-// them before a decode step has written them.  Measured beside the other
-// model's forward (8176 rows, Qwen-shaped senior; 4056 rows, small senior): one
-// row and head per wave 232 and 35 us, this kernel 103 and 13 us.
+// them before a decode step has written them.  A wave's 16 rows are a chain, K
+// slice by K slice, that only a full device hides (see launch_qkv_post).
+// Measured alone, us, this kernel against one row and head per wave: 8184 rows
+// of the Qwen-shaped senior 91 and 190, junior 62 and 113, small senior 21 and
+// 51; 2039 rows 26 and 37, 18 and 23, 8 and 14.
 template <int HD>
 __global__ __launch_bounds__(kNT) void qkv_prompt_kernel(
     const float* __restrict__ ws, int S, long ws_stride, int nq, int nkv, const float* __restrict__ q_norm,
@@ -915,7 +917,13 @@ hipError_t launch_qkv_post(const QkvPostArgs& a, hipStream_t st) {
   if (a.R <= 0) return hipSuccess;
   if (a.S > kSplitMaxDev || a.hd > 128) return hipErrorInvalidValue;
   const int hb = (a.nq + 2 * a.nkv + kNT / 64 - 1) / (kNT / 64);
-  if (a.dt == DT_BF16 && a.grp_row0) {               // prompt rows in groups of one cache chunk
+  // Prompt rows in groups of one cache chunk, from 5 rows per compute unit on.  On
+  // both sides of the line, us by groups and by rows: 1535 rows 23.0 and 27.2
+  // (Qwen-shaped senior), 17.1 and 18.3 (junior), 7.5 and 11.2, 8.5 and 8.0 (small
+  // pair); 1023 rows 22.4 and 19.0, 16.6 and 13.5, 7.8 and 8.5, 9.1 and 6.5; 17
+  // rows, whose projection has 10 to 16 K slices, 18.8 and 3.8, 17.4 and 3.8, 7.4
+  // and 3.4, 5.7 and 3.2.
+  if (a.dt == DT_BF16 && a.grp_row0 && a.R >= 5 * a.n_cu) {
     auto run = [&](auto kernel) {
       hipLaunchKernelGGL(kernel, dim3(a.n_groups, hb), dim3(kNT), 0, st, a.ws, a.S, a.ws_stride, a.nq, a.nkv, a.q_norm,
                          a.k_norm, a.eps, a.rope, a.row_slot, a.row_pos, a.grp_row0, a.grp_n, a.q_out,

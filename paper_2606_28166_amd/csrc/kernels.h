@@ -139,6 +139,7 @@ struct QkvPostArgs {
   // prompt rows: n_groups groups of at most 16 consecutive rows of one prompt
   // (one 16-position chunk each); NULL at decode
   const int32_t* grp_row0; const int32_t* grp_n; int n_groups;
+  int n_cu;               // compute units of the device
 };
 hipError_t launch_qkv_post(const QkvPostArgs& a, hipStream_t st);
 

@@ -548,7 +548,7 @@ tandem_status forward_layer(tandem_handle* h, Model& m, int l, const FwdRows& fr
     qp.eps = c.rms_eps; qp.rope = m.rope;
     qp.row_slot = fr.slot; qp.row_pos = fr.pos; qp.row_done = fr.done;
     qp.q_out = m.q; qp.cache = cg;
-    qp.grp_row0 = fr.grp_row0; qp.grp_n = fr.grp_n; qp.n_groups = fr.n_groups;
+    qp.grp_row0 = fr.grp_row0; qp.grp_n = fr.grp_n; qp.n_groups = fr.n_groups; qp.n_cu = h->n_cu;
     TIMED(TANDEM_K_OTHER, launch_qkv_post(qp, st));
   }
 

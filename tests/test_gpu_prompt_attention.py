@@ -1,6 +1,7 @@
-"""GPU parity of the prompt attention at the edges of its row groups (16 rows)
-and stages (32 positions), for each head size and group size it has a kernel
-for, through the C ABI.
+"""GPU parity of the prompt rows' QKV post-processing and attention at the edges
+of their row groups (16 rows) and stages (32 positions), for each head size and
+group size they have a kernel for, through the C ABI: a few prompts at a time,
+and many in one pass (5 rows and more per compute unit).
 
 The first step after the prefill attends to every prompt position, so its logits
 see the prompt's K/V of both layers, and the second layer's K/V sees the first
@@ -33,4 +34,17 @@ def test_prompt_attention_edges(hd, gqa_sen, gqa_jun):
     ws, wj, _, bnd = W.make_all(wl)
     prompts = [W.make_prompts(wl)[i][:n] for i, n in enumerate(LENGTHS)]
     p = P.run(wl, logits_at=(1, 2), max_prefill_tokens=256, weights=(ws, wj, prompts, bnd))
+    P.check(p, P.TOL_BF16)
+
+
+@pytest.mark.parametrize("hd,gqa_sen,gqa_jun", [(32, 4, 2), (64, 4, 2), (128, 4, 2), (64, 8, 1), (128, 1, 8)])
+def test_many_prompt_rows_in_one_pass(hd, gqa_sen, gqa_jun):
+    lengths = LENGTHS * 8                               # 3464 rows
+    P.log(f"case prompt rows: head_dim {hd}, groups of {gqa_sen} and {gqa_jun} heads, {len(lengths)} prompts")
+    wl = _pair(hd, gqa_sen, gqa_jun, lengths)
+    wl.junior.n_kv_heads, wl.junior.n_q_heads = 2, 2 * gqa_jun
+    ws, wj, _, bnd = W.make_all(wl)
+    prompts = [p[:n] for p, n in zip(W.make_prompts(wl), lengths)]
+    rows = list(range(0, 96, 7)) + [95]
+    p = P.run(wl, logits_at=(1, 2), max_prefill_tokens=4096, weights=(ws, wj, prompts, bnd), seq_subset=rows)
     P.check(p, P.TOL_BF16)
