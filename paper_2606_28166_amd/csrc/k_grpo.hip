@@ -130,8 +130,10 @@ __global__ __launch_bounds__(NT) void grpo_terms_kernel(GrpoArgs a) {
     }
     a.adv[s] = A;
     a.cnt[s] = (int32_t)n;
-    a.part[s] = (float)sum;
-    if (a.part_lo) a.part_lo[s] = (float)(sum - (double)(float)sum);
+    const float hi = (float)sum;
+    a.part[s] = hi;
+    // an infinite sum (a ratio that overflows) leaves no remainder: inf - inf is NaN
+    if (a.part_lo) a.part_lo[s] = fabsf(hi) < INFINITY ? (float)(sum - (double)hi) : 0.f;
   }
 }
 

@@ -93,6 +93,31 @@ def test_grpo_ratio_one_no_gradient_and_empty_mask():
     assert np.all(got["grad"] == 0.0)
 
 
+@pytest.mark.parametrize("T", [300, 1024, 1025, 3000])
+def test_grpo_ratio_that_overflows(T):
+    """A position whose log-probs lie 120 apart: the ratio is infinite in
+    float32, so with a negative advantage the loss is +inf (the term is the
+    unclipped one) and that position's gradient too; with a positive one the term
+    is the clipped constant.  Every other position keeps its gradient."""
+    P.log(f"case grpo loss: infinite ratio, stride {T}")
+    r, o, l, lo, ln = W.make_grpo_batch(2, 4, T, seed=17)
+    r[:4], l[:4] = [0, 1, 1, 1], T                      # rollout 0 has the negative advantage of its group
+    for s, loss in ((1, None), (0, np.inf)):
+        o2, ln2 = o.copy(), ln.copy()
+        o2[s, T // 2] = 1
+        ln2[s, T // 2] = lo[s, T // 2] + 120.0
+        got = _gpu(r, o2, l, lo, ln2, 4)
+        adv, mask = group_advantages(r, 4), senior_mask(o2, l)
+        if loss is None:                                # the clipped term: (1 + eps) A
+            ref, n, _ = clipped_loss(ln2, lo, adv, mask, EPS)
+            assert int(got["n_masked"][0]) == n
+            assert abs(float(got["loss"][0]) - ref) <= 1e-5 * np.abs(adv).max() * 2
+            assert got["grad"][s, T // 2] == 0.0 and np.isfinite(got["grad"]).all()
+        else:
+            assert float(got["loss"][0]) == loss and got["grad"][s, T // 2] == loss
+            assert np.isfinite(np.delete(got["grad"].ravel(), s * T + T // 2)).all()
+
+
 def test_grpo_zero_clip_band_and_out_of_range_lengths():
     """eps = 0 (the band collapses to ratio 1: a term keeps its gradient only
     on the side the sign of A allows) and lengths outside [0, T] (clamped:
