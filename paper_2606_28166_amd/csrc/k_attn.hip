@@ -1,6 +1,7 @@
 // Grouped-query attention of one new query position per row over that row's
 // KV cache (decode), and of prompt rows (each prompt token attends to positions
-// 0..its own position of the prompt's cache; see attn_prompt_kernel).
+// 0..its own position of the prompt's cache; see attn_prompt_kernel and, for
+// prompts that leave the device partly idle, attn_mfma_kernel).
 //
 // bf16 decode (HD in {64, 128}): one workgroup per (kv head, row); its four
 // waves take interleaved 16-position chunks of the tiled cache and keep
@@ -20,6 +21,7 @@
 // fp32 path: a plain VALU kernel, one workgroup per (query head, row).
 #include "common.h"
 #include "kernels.h"
+#include "tile_plan.h"
 
 
 namespace tandem {
@@ -89,11 +91,14 @@ struct AttnState {
   f32x4_t o[HD / 16];             // O[head 4g + i][dim 16 db + c16]
 };
 
-// ctx: the row attends positions < ctx (later ones hold stale cache contents).
+// ctx: this lane's query column attends positions < ctx; ctx_max: positions
+// >= ctx_max hold stale cache contents.  GUARD: a column may see a chunk with
+// no position it attends before any it does (several query rows per
+// workgroup); its running max then stays -inf and nothing is added.
 // First half of a chunk: scores of its 16 positions from the K tile, the
 // online-softmax update and the rescaling of the accumulator; returns the
 // probabilities as split bf16 operands of the value product.
-template <int HD>
+template <int HD, bool GUARD>
 __device__ __forceinline__ void attend_scores(AttnState<HD>& st, const Half<HD>& k, const bf16x8_t* qh,
                                               const bf16x8_t* ql, int p0, int ctx, float scale, int g, s16x4_t& ph,
                                               s16x4_t& pl) {
@@ -114,10 +119,11 @@ __device__ __forceinline__ void attend_scores(AttnState<HD>& st, const Half<HD>&
   mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
   mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
   const float m_new = fmaxf(st.m_run, mx);
-  const float alpha = exp2f(st.m_run - m_new);
+  const bool none = GUARD && m_new == -INFINITY;
+  const float alpha = none ? 1.f : exp2f(st.m_run - m_new);
   float pr[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) pr[i] = exp2f(s[i] - m_new);
+  for (int i = 0; i < 4; ++i) pr[i] = none ? 0.f : exp2f(s[i] - m_new);
   st.l_run = st.l_run * alpha + ((pr[0] + pr[1]) + (pr[2] + pr[3]));
   st.m_run = m_new;
   split4(pr, ph, pl);
@@ -136,14 +142,14 @@ __device__ __forceinline__ void attend_scores(AttnState<HD>& st, const Half<HD>&
 // Second half of a chunk: the probabilities times its V tile.
 template <int HD>
 __device__ __forceinline__ void attend_values(AttnState<HD>& st, Half<HD>& v, s16x4_t ph, s16x4_t pl, int p0,
-                                              int ctx, int g) {
+                                              int ctx_max, int g) {
   constexpr int DC = HD / 32, DB = HD / 16;
   const int pg = p0 + 4 * g;
   // positions at or past the context hold stale cache contents: zero them so
   // that 0 * (stale) cannot produce NaN
-  if (p0 + 16 > ctx) {
+  if (p0 + 16 > ctx_max) {
     // keep the first nv of this lane's four positions (16 bits each)
-    const int nv = min(max(ctx - pg, 0), 4);
+    const int nv = min(max(ctx_max - pg, 0), 4);
     const uint64_t keep = nv == 4 ? ~0ull : (1ull << (16 * nv)) - 1ull;
     const uint32_t klo = (uint32_t)keep, khi = (uint32_t)(keep >> 32);
 #pragma unroll
@@ -164,24 +170,30 @@ __device__ __forceinline__ void attend_values(AttnState<HD>& st, Half<HD>& v, s1
   }
 }
 
-// One workgroup's attention of one row: query columns c < GQA are the heads
-// kh GQA + c, over positions [0, ctx) of one slot's tiled K/V plane of kv head
-// kh.  The four waves take interleaved 16-position chunks with their own online
-// softmax and leave their states in LDS: sm_m[w][c] (running max, log2 units),
-// sm_l[w][c] (sum of exponentials), sm_o[(w GQA + c) HD + d] (unnormalised
-// weighted sums).
-template <int HD, int GQA>
+// One workgroup's attention of ROWS consecutive rows of one sequence (nr of them
+// used): query column c is row r0 + c / GQA, head kh GQA + c % GQA, over positions
+// [0, ctx_max) of one slot's tiled K/V plane of kv head kh; with ROWS > 1 a column
+// attends those up to its own row's position.  The four waves take interleaved
+// 16-position chunks with their own online softmax and leave their states in
+// LDS: sm_m[w][c] (running max, log2 units), sm_l[w][c] (sum of exponentials),
+// sm_o[(w NCOL + c) HD + d] (unnormalised weighted sums), NCOL = GQA ROWS.
+template <int HD, int GQA, int ROWS>
 __device__ __forceinline__ void attend_block(const float* __restrict__ q, const bf16_t* __restrict__ kc,
                                              const bf16_t* __restrict__ vc, int ctx_stride, long slot_stride,
-                                             int slot, int kh, int row, int ctx, int nq, float (*sm_m)[16],
+                                             int slot, int kh, int r0, int nr, int ctx_max,
+                                             const int32_t* __restrict__ row_pos, int nq, float (*sm_m)[16],
                                              float (*sm_l)[16], float* sm_o, int pslot = 0, int lo16 = 0) {
   constexpr int DC = HD / 32;     // k-steps of the S product
   constexpr int DB = HD / 16;     // 16-dim blocks of the O product
-  static_assert(GQA <= 16, "16 query columns per workgroup");
+  constexpr int NCOL = GQA * ROWS;
+  static_assert(NCOL <= 16, "16 query columns per workgroup");
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: the chunk branches stay scalar
   const int g = lane >> 4, c16 = lane & 15;
-  const bool valid = c16 < GQA;                       // this lane's query column
+  const int ri = ROWS > 1 ? c16 / GQA : 0;            // this lane's query column
+  const bool valid = c16 < NCOL && ri < nr;
+  const int rr = r0 + (valid ? ri : 0);
+  const int ctx = ROWS > 1 && valid ? row_pos[rr] + 1 : ctx_max;   // positions the column attends
   const size_t plane = (size_t)slot * slot_stride + (size_t)kh * ctx_stride * HD;
   const __amdgpu_buffer_rsrc_t kr_o = buf_rsrc(kc + plane, (uint32_t)ctx_stride * HD * 2);
   const __amdgpu_buffer_rsrc_t vr_o = buf_rsrc(vc + plane, (uint32_t)ctx_stride * HD * 2);
@@ -197,7 +209,7 @@ __device__ __forceinline__ void attend_block(const float* __restrict__ q, const 
   // requested first and its first three chunks right after, behind a
   // compiler barrier, so that waiting for the query (the wait counter is in
   // issue order) leaves the chunks in flight.
-  const float* qp = q + ((size_t)row * nq + kh * GQA + (valid ? c16 : 0)) * HD + 8 * g;
+  const float* qp = q + ((size_t)rr * nq + kh * GQA + (valid ? c16 - ri * GQA : 0)) * HD + 8 * g;
   float4 qa[DC], qb[DC];
 #pragma unroll
   for (int dc = 0; dc < DC; ++dc) {
@@ -205,7 +217,7 @@ __device__ __forceinline__ void attend_block(const float* __restrict__ q, const 
     qb[dc] = *reinterpret_cast<const float4*>(qp + 32 * dc + 4);
   }
   asm volatile("" : : : "memory");
-  const int nchunk = (ctx + 15) >> 4;
+  const int nchunk = (ctx_max + 15) >> 4;
   const int nmine = nchunk > wave ? (nchunk - wave + 3) >> 2 : 0;
   auto chunk_at = [&](int i) { return wave + 4 * min(i, nmine - 1); };
   // Six half-chunk slots, three chunks: the K and V tiles of chunk i live in
@@ -253,11 +265,11 @@ __device__ __forceinline__ void attend_block(const float* __restrict__ q, const 
     const int p0 = 16 * chunk_at(j);
     s16x4_t ph, pl;
     pin_half<HD>(ks);
-    attend_scores<HD>(st, ks, qh, ql, p0, ctx, scale, g, ph, pl);
+    attend_scores<HD, (ROWS > 1)>(st, ks, qh, ql, p0, ctx, scale, g, ph, pl);
     pin_half<HD>(ks);
     load_half<HD>(ks, kr(src(j + 3)), src(j + 3), lane);
     pin_half<HD>(vs);
-    attend_values<HD>(st, vs, ph, pl, p0, ctx, g);
+    attend_values<HD>(st, vs, ph, pl, p0, ctx_max, g);
     pin_half<HD>(vs);
     load_half<HD>(vs, vr(src(j + 3)), src(j + 3), lane);
   };
@@ -285,7 +297,7 @@ __device__ __forceinline__ void attend_block(const float* __restrict__ q, const 
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int h = 4 * g + i;
-      if (h < GQA) sm_o[(wave * GQA + h) * HD + db * 16 + c16] = st.o[db][i];
+      if (h < NCOL) sm_o[(wave * NCOL + h) * HD + db * 16 + c16] = st.o[db][i];
     }
   __syncthreads();
 }
@@ -311,28 +323,42 @@ __device__ __forceinline__ void waves_merged(const float (*sm_m)[16], const floa
 }
 
 // One workgroup per (kv head, row), query columns = the GQA heads of the group:
-// decode rows, and prompt rows of 16-head groups (row_done NULL).
-template <int HD, int GQA>
+// decode rows, and prompt rows of 16-head groups (row_done NULL).  ROWS = 16 /
+// GQA > 1: prompt rows that leave the device partly idle (see
+// prompt_splits_positions), ROWS consecutive rows of a group per workgroup, each
+// column with its own causal limit; a group of at most 16 rows is split over GQA
+// workgroups.
+template <int HD, int GQA, int ROWS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void attn_mfma_kernel(
     const float* __restrict__ q, const bf16_t* __restrict__ kc, const bf16_t* __restrict__ vc,
     int ctx_stride, long slot_stride, const int32_t* __restrict__ row_slot,
     const int32_t* __restrict__ row_pos, const int32_t* __restrict__ row_done,
-    bf16_t* __restrict__ out, int nq) {
+    const int32_t* __restrict__ grp_row0, const int32_t* __restrict__ grp_n, bf16_t* __restrict__ out, int nq) {
+  constexpr int NCOL = GQA * ROWS;
   __shared__ float sm_m[4][16];
   __shared__ float sm_l[4][16];
-  __shared__ float sm_o[4 * GQA * HD];
-  const int kh = blockIdx.x, r = blockIdx.y, tid = threadIdx.x;
-  const int col0 = kh * GQA * HD;
-  bf16_t* orow = out + (size_t)r * 2 * nq * HD;      // split-format activation row
-  if (row_done && row_done[r]) {
+  __shared__ float sm_o[4 * NCOL * HD];
+  const int kh = blockIdx.x, tid = threadIdx.x, col0 = kh * GQA * HD;
+  int r0 = blockIdx.y, nr = 1;
+  if (ROWS > 1) {
+    const int grp = blockIdx.y / GQA, sub = blockIdx.y % GQA;
+    r0 = grp_row0[grp] + sub * ROWS;
+    nr = min(ROWS, grp_n[grp] - sub * ROWS);
+    if (nr <= 0) return;
+  }
+  if (ROWS == 1 && row_done && row_done[r0]) {
+    bf16_t* orow = out + (size_t)r0 * 2 * nq * HD;   // split-format activation row
     for (int e = tid; e < GQA * HD; e += 256) split_store(orow, col0 + e, 0.f);
     return;
   }
-  attend_block<HD, GQA>(q, kc, vc, ctx_stride, slot_stride, row_slot[r], kh, r, row_pos[r] + 1, nq, sm_m, sm_l, sm_o);
-  for (int e = tid; e < GQA * HD; e += 256) {
+  attend_block<HD, GQA, ROWS>(q, kc, vc, ctx_stride, slot_stride, row_slot[r0], kh, r0, nr, row_pos[r0 + nr - 1] + 1,
+                              row_pos, nq, sm_m, sm_l, sm_o);
+  for (int e = tid; e < NCOL * HD; e += 256) {
+    const int c = e / HD, d = e % HD;
+    if (c / GQA >= nr) continue;
     float M, num, den;
-    waves_merged<HD, GQA>(sm_m, sm_l, sm_o, e / HD, e % HD, M, num, den);
-    split_store(orow, col0 + e, num / den);
+    waves_merged<HD, NCOL>(sm_m, sm_l, sm_o, c, d, M, num, den);
+    split_store(out + (size_t)(r0 + c / GQA) * 2 * nq * HD, col0 + (c % GQA) * HD + d, num / den);
   }
 }
 
@@ -358,8 +384,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
     return;
   }
   const int lo = row_lo[r];
-  attend_block<HD, GQA>(q, kc, vc, ctx_stride, slot_stride, row_slot[r], kh, r, row_pos[r] + 1, nq, sm_m, sm_l, sm_o,
-                        lo > 0 ? pfx_slot[r] : 0, lo >> 4);
+  attend_block<HD, GQA, 1>(q, kc, vc, ctx_stride, slot_stride, row_slot[r], kh, r, 1, row_pos[r] + 1, row_pos, nq, sm_m,
+                           sm_l, sm_o, lo > 0 ? pfx_slot[r] : 0, lo >> 4);
   for (int e = tid; e < GQA * HD; e += 256) {
     float M, num, den;
     waves_merged<HD, GQA>(sm_m, sm_l, sm_o, e / HD, e % HD, M, num, den);
@@ -376,11 +402,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
 // of a stage make one k-range of a 16x16x32 MFMA in the value product: k-value
 // 4 t + e of lane group g is position 16 t + 4 g + e of the stage, which is
 // where both the scores' accumulators and the cache's V tile have it.
+// A wave walks every position of the prompt, about 1 us per stage, which other
+// workgroups have to hide: prompt_splits_positions says from where on they do.
 // Measured (16 prompts of 511 rows, two layers of each of the Qwen-shaped models,
 // the four launches): the kernel with 16 columns per workgroup, whose waves split
 // the positions, 1100 us; this one 550.
 template <int HD, int GQA>
-__global__ __launch_bounds__(64 * GQA) __attribute__((amdgpu_waves_per_eu(GQA == 1 ? 1 : 2))) void attn_prompt_kernel(
+__global__ __launch_bounds__(64 * GQA) __attribute__((amdgpu_waves_per_eu(2))) void attn_prompt_kernel(
     const float* __restrict__ q, const bf16_t* __restrict__ kc, const bf16_t* __restrict__ vc, int ctx_stride,
     long slot_stride, const int32_t* __restrict__ row_slot, const int32_t* __restrict__ row_pos,
     const int32_t* __restrict__ grp_row0, const int32_t* __restrict__ grp_n, bf16_t* __restrict__ out, int nq) {
@@ -633,10 +661,18 @@ hipError_t run_mfma(const AttnArgs& a, hipStream_t st) {
   const bf16_t* vc = (const bf16_t*)a.cache.v;
   if constexpr (GQA <= 8) {
     if (a.grp_row0) {                   // prompt rows
-      hipLaunchKernelGGL((attn_prompt_kernel<HD, GQA>), dim3(a.nkv, a.n_groups), dim3(64 * GQA), 0, st, a.q, kc, vc,
-                         a.cache.ctx_stride, a.cache.slot_stride, a.row_slot, a.row_pos, a.grp_row0, a.grp_n,
-                         (bf16_t*)a.out, a.nq);
-      return hipGetLastError();
+      if (prompt_splits_positions(a.n_cu, a.nkv, GQA, HD, a.n_groups, a.grp_ctx)) {
+        hipLaunchKernelGGL((attn_mfma_kernel<HD, GQA, 16 / GQA>), dim3(a.nkv, a.n_groups * GQA), dim3(256), 0, st, a.q,
+                           kc, vc, a.cache.ctx_stride, a.cache.slot_stride, a.row_slot, a.row_pos, a.row_done,
+                           a.grp_row0, a.grp_n, (bf16_t*)a.out, a.nq);
+        return hipGetLastError();
+      }
+      if constexpr (GQA > 1) {          // (groups of one head never come here)
+        hipLaunchKernelGGL((attn_prompt_kernel<HD, GQA>), dim3(a.nkv, a.n_groups), dim3(64 * GQA), 0, st, a.q, kc, vc,
+                           a.cache.ctx_stride, a.cache.slot_stride, a.row_slot, a.row_pos, a.grp_row0, a.grp_n,
+                           (bf16_t*)a.out, a.nq);
+        return hipGetLastError();
+      }
     }
   }
   if (a.row_lo) {                       // decode rows with a shared prompt prefix
@@ -646,8 +682,9 @@ hipError_t run_mfma(const AttnArgs& a, hipStream_t st) {
                        a.pfx_slot, (bf16_t*)a.out, a.nq);
     return hipGetLastError();
   }
-  hipLaunchKernelGGL((attn_mfma_kernel<HD, GQA>), dim3(a.nkv, a.R), dim3(256), 0, st, a.q, kc, vc,
-                     a.cache.ctx_stride, a.cache.slot_stride, a.row_slot, a.row_pos, a.row_done, (bf16_t*)a.out, a.nq);
+  hipLaunchKernelGGL((attn_mfma_kernel<HD, GQA, 1>), dim3(a.nkv, a.R), dim3(256), 0, st, a.q, kc, vc,
+                     a.cache.ctx_stride, a.cache.slot_stride, a.row_slot, a.row_pos, a.row_done,
+                     (const int32_t*)nullptr, (const int32_t*)nullptr, (bf16_t*)a.out, a.nq);
   return hipGetLastError();
 }
 

@@ -156,6 +156,8 @@ struct AttnArgs {
   // rows of one prompt, rows grp_row0[g] .. + grp_n[g] - 1 in increasing
   // position order; NULL: one workgroup per row
   const int32_t* grp_row0; const int32_t* grp_n; int n_groups;
+  int grp_ctx;            // positions of the longest of these prompts
+  int n_cu;               // compute units this launch may count on
   // Decode rows whose prompt prefix is shared (row_lo != NULL; needs
   // row_done): row r attends positions [0, row_lo[r]) in slot pfx_slot[r]
   // and [row_lo[r], row_pos[r]] in its own slot; row_lo is a multiple of 16

@@ -1,4 +1,5 @@
-"""Address arithmetic of the tiled GEMM, compiled for the host and enumerated."""
+"""Address arithmetic of the tiled GEMM and the choice between the prompt attentions, compiled for the host and
+enumerated."""
 import os
 import subprocess
 
@@ -44,3 +45,31 @@ def _run(tmp_path, source):
 
 def test_weight_fragments_lie_inside_the_matrix(tmp_path):
     _run(tmp_path, OFFSETS)
+
+
+ATTENTION = r"""
+#include <cstdio>
+#include "tile_plan.h"
+// {kv heads, heads per group, head size, row groups, longest prompt, waves that split the positions}
+int main() {
+  const int c[][6] = {
+      {4, 4, 64, 32, 512, 1},  {4, 4, 64, 128, 2040, 1},  {4, 4, 64, 512, 2040, 0}, {4, 4, 64, 128, 512, 0},
+      {4, 4, 64, 64, 128, 0},  {4, 4, 64, 256, 256, 0},   {8, 4, 128, 8, 128, 1},   {8, 4, 128, 128, 2040, 0},
+      {8, 2, 128, 32, 512, 1}, {8, 2, 128, 512, 2040, 0}, {2, 8, 64, 128, 2040, 1}, {2, 8, 64, 128, 512, 0},
+      {8, 1, 128, 8, 128, 1},  {8, 1, 128, 512, 2040, 1},
+      // the GPU parity cases: a few prompts (up to 20 groups a pass), then 240 groups
+      {2, 4, 64, 20, 96, 1},   {2, 4, 128, 20, 96, 1},    {1, 2, 128, 20, 96, 1},   {2, 8, 64, 20, 96, 1},
+      {1, 8, 128, 20, 96, 1},  {2, 4, 64, 240, 96, 0},    {2, 2, 64, 240, 96, 0},   {2, 4, 128, 240, 96, 0},
+      {2, 2, 128, 240, 96, 0}, {2, 8, 64, 240, 96, 0},    {2, 8, 128, 240, 96, 0}};
+  for (const auto& x : c)
+    if (tandem::prompt_splits_positions(256, x[0], x[1], x[2], x[3], x[4]) != (x[5] != 0)) {
+      printf("%d kv heads, groups of %d, head size %d, %d row groups, %d positions\n", x[0], x[1], x[2], x[3], x[4]);
+      return 1;
+    }
+  return 0;
+}
+"""
+
+
+def test_prompt_attention_of_each_shape(tmp_path):
+    _run(tmp_path, ATTENTION)
