@@ -585,7 +585,11 @@ __global__ __launch_bounds__(64 * GQA) __attribute__((amdgpu_waves_per_eu(2))) v
   }
 }
 
-template <typename KT, bool SPLIT>
+// Any other model: a workgroup per (head, row), 128 positions at a time.  PARTS:
+// the value product's threads are (part, dim), part = thread / hd, and take
+// positions part, part + 128 / hd, .. of a block, several loads in flight: for
+// launches that leave the device idle (see launch_attention).
+template <typename KT, bool SPLIT, bool PARTS>
 __global__ __launch_bounds__(128) void attn_valu_kernel(
     const float* __restrict__ q, const KT* __restrict__ kc, const KT* __restrict__ vc, int hd,
     int ctx_stride, long slot_stride, const int32_t* __restrict__ row_slot,
@@ -609,9 +613,7 @@ __global__ __launch_bounds__(128) void attn_valu_kernel(
   __syncthreads();
   const float scale = 1.f / sqrtf((float)hd);
   float m_run = -INFINITY, l_run = 0.f, o = 0.f;
-  // the value product: thread (part, dim) takes positions part, part + parts, ..
-  // of a block, several loads in flight
-  const int parts = 128 / hd, part = tid / hd, dim = tid % hd;
+  const int parts = PARTS ? 128 / hd : 1, part = PARTS ? tid / hd : 0, dim = PARTS ? tid % hd : tid;
   for (int p0 = 0; p0 < ctx; p0 += 128) {
     const int p = p0 + tid;
     float s = -INFINITY;
@@ -636,15 +638,23 @@ __global__ __launch_bounds__(128) void attn_valu_kernel(
     __syncthreads();
     ls = red[0] + red[1];
     l_run = l_run * alpha + ls;
-    if (part < parts) {
+    if (PARTS ? part < parts : tid < hd) {
       const int n = min(128, ctx - p0);
       float acc = 0.f;
+      if (PARTS) {
 #pragma unroll 8
-      for (int t = part; t < n; t += parts) acc += sp[t] * ld(vbase + kv_v_index(p0 + t, dim, hd));
+        for (int t = part; t < n; t += parts) acc += sp[t] * ld(vbase + kv_v_index(p0 + t, dim, hd));
+      } else {
+        for (int t = 0; t < n; ++t) acc += sp[t] * ld(vbase + kv_v_index(p0 + t, tid, hd));
+      }
       o = o * alpha + acc;
     }
     m_run = m_new;
     __syncthreads();
+  }
+  if (!PARTS) {
+    if (tid < hd) act_store<SPLIT>(out, r, width, h * hd + tid, o / l_run);
+    return;
   }
   sp[tid] = o;
   __syncthreads();
@@ -716,14 +726,30 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t st) {
     return dispatch_gqa<128>(a, gqa, st);
   }
   if (a.hd > 128) return hipErrorInvalidValue;
-  if (a.dt == DT_BF16)
-    hipLaunchKernelGGL((attn_valu_kernel<bf16_t, true>), dim3(a.nq, a.R), dim3(128), 0, st, a.q,
-                       (const bf16_t*)a.cache.k, (const bf16_t*)a.cache.v, a.hd, a.cache.ctx_stride,
+  // The value product in parts is faster while its workgroups' value tiles are
+  // below about 1 KB per compute unit and position block, and up to 2.7 times
+  // slower on a full device.  us, in parts / whole: float32, 4 heads of 32, 16 rows of
+  // 300 positions 16.8 / 28.6, prompts of 512 rows 41 / 47, 1024 rows 134 / 90;
+  // float32, 16 heads of 64, 32 rows of 300 31.5 / 39.4, 64 rows 50.6 / 44.4, 1024
+  // prompt rows 964 / 352; bf16, 12 heads of 64, 128 prompt rows 15.4 / 18.8, 256 rows
+  // 33.7 / 32.9.  With head size 128 there is one part, whose deeper unrolling helps
+  // bf16 (24 heads, 16 rows of 2000 positions 240 / 277, 64 rows of 300 73 / 61) and not
+  // float32 (8 heads, one row of 300 34.5 / 30.9).
+  const size_t esz = a.dt == DT_BF16 ? 2 : 4;
+  const bool parts = (a.hd < 128 || a.dt == DT_BF16) && (size_t)a.nq * a.R * a.hd * esz < (size_t)a.n_cu * 1024;
+  auto run = [&](auto kernel, auto* kc, auto* vc) {
+    hipLaunchKernelGGL(kernel, dim3(a.nq, a.R), dim3(128), 0, st, a.q, kc, vc, a.hd, a.cache.ctx_stride,
                        a.cache.slot_stride, a.row_slot, a.row_pos, a.row_done, a.out, a.nq, a.nkv);
-  else
-    hipLaunchKernelGGL((attn_valu_kernel<float, false>), dim3(a.nq, a.R), dim3(128), 0, st, a.q,
-                       (const float*)a.cache.k, (const float*)a.cache.v, a.hd, a.cache.ctx_stride,
-                       a.cache.slot_stride, a.row_slot, a.row_pos, a.row_done, a.out, a.nq, a.nkv);
+  };
+  if (a.dt == DT_BF16) {
+    const bf16_t *kc = (const bf16_t*)a.cache.k, *vc = (const bf16_t*)a.cache.v;
+    if (parts) run(attn_valu_kernel<bf16_t, true, true>, kc, vc);
+    else run(attn_valu_kernel<bf16_t, true, false>, kc, vc);
+  } else {
+    const float *kc = (const float*)a.cache.k, *vc = (const float*)a.cache.v;
+    if (parts) run(attn_valu_kernel<float, false, true>, kc, vc);
+    else run(attn_valu_kernel<float, false, false>, kc, vc);
+  }
   return hipGetLastError();
 }
 

@@ -48,3 +48,18 @@ def test_many_prompt_rows_in_one_pass(hd, gqa_sen, gqa_jun):
     rows = list(range(0, 96, 7)) + [95]
     p = P.run(wl, logits_at=(1, 2), max_prefill_tokens=4096, weights=(ws, wj, prompts, bnd), seq_subset=rows)
     P.check(p, P.TOL_BF16)
+
+
+@pytest.mark.parametrize("hd,dtype", [(32, "f32"), (64, "f32"), (128, "f32"), (32, "bf16"), (64, "bf16")])
+def test_plain_attention_of_many_and_few_rows(hd, dtype):
+    """Groups of three heads (and float32) take the plain attention: the prompts'
+    rows in one pass the form for a full device, the steps' 14 rows the one whose
+    value product is in parts; contexts of up to three 128-position blocks."""
+    lengths = LENGTHS + [130, 260]
+    P.log(f"case plain attention: head_dim {hd}, {dtype}, prompt lengths {lengths}")
+    wl = _pair(hd, 3, 3, lengths)
+    wl.senior.dtype = wl.junior.dtype = dtype
+    ws, wj, _, bnd = W.make_all(wl)
+    prompts = [p[:n] for p, n in zip(W.make_prompts(wl), lengths)]
+    p = P.run(wl, logits_at=(1, 2), max_prefill_tokens=1024, weights=(ws, wj, prompts, bnd))
+    P.check(p, P.TOL_F32 if dtype == "f32" else P.TOL_BF16)
