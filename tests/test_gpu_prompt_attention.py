@@ -50,7 +50,8 @@ def test_many_prompt_rows_in_one_pass(hd, gqa_sen, gqa_jun):
     P.check(p, P.TOL_BF16)
 
 
-@pytest.mark.parametrize("hd,dtype", [(32, "f32"), (64, "f32"), (128, "f32"), (32, "bf16"), (64, "bf16")])
+@pytest.mark.parametrize("hd,dtype", [(32, "f32"), (64, "f32"), (128, "f32"), (32, "bf16"), (64, "bf16"),
+                                      (128, "bf16")])
 def test_plain_attention_of_many_and_few_rows(hd, dtype):
     """Groups of three heads (and float32) take the plain attention: the prompts'
     rows in one pass the form for a full device, the steps' 14 rows the one whose
