@@ -446,6 +446,14 @@ __global__ __launch_bounds__(kNT) void sample_partials_kernel(SampleArgs a) {
       }
     }
   }
+  // no score above -inf: the first entry at -inf (NaN scores beat nothing)
+  if (top.i == 0x7FFFFFFF && v0 + 4 * tid < v1) {
+#pragma unroll
+    for (int i = 4 * kVocabQuads - 1; i >= 0; --i) {
+      const int v = v0 + 4 * (kNT * (i >> 2) + tid) + (i & 3);
+      if (v < v1 && (own_sen ? x[i] : y[i]) == -INFINITY) top.i = v;
+    }
+  }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
     const float m2 = __shfl_xor(ms, o, 64), l2 = __shfl_xor(ls, o, 64);

@@ -112,3 +112,31 @@ def test_a_temperature_whose_reciprocal_overflows():
     owner_z = np.where(own[:, None] != 0, z["senior"], z["junior"])
     np.testing.assert_array_equal(dbg["sampled"][:n].cpu().numpy(), owner_z.argmax(1))
     eng.close()
+
+
+@pytest.mark.parametrize("first", [1, 5, 4100])
+def test_no_score_above_minus_infinity(first):
+    """T = 1e-39 and one logit for all entries, about -1 for some rows: their
+    scores are all -inf, and NaN up to entry `first`.  The library's sample is the
+    first entry that is not NaN."""
+    from paper_2606_28166_amd.engine import TandemEngine
+    P.log(f"case every score -inf from entry {first} on, NaN below")
+    wl = W.workload("tiny").replace(gain_jitter=0.1, n_prompts=8, group=2, prompt_len=5)
+    wl.senior.vocab = wl.junior.vocab = 4300
+    wl.sample = W.SampleSettings(1e-39, -1, 0.0, 0.0, 2)
+    ws, wj, prompts, _ = W.make_all(wl)
+    for w in (ws, wj):
+        w["lm_head"][:] = w["lm_head"][4200] * np.float32(50)
+        w["lm_head"][:first, 0] = np.nan
+    n = wl.n_seqs
+    eng = TandemEngine(wl.senior, ws, wl.junior, wj, wl.switch, wl.sample, wl.philox_seed, max_seqs=n, max_ctx=16)
+    eng.prefill(prompts, wl.group)
+    own = eng.state()["owner"]
+    dbg = eng.step_forced(np.arange(n), logits=True)
+    z = {k: dbg[f"logits_{k}"][:n].cpu().numpy() for k in ("senior", "junior")}
+    owner_z = np.where(own[:, None] != 0, z["senior"], z["junior"])
+    assert np.isnan(owner_z[:, :first]).all()
+    low = (owner_z[:, first:] < -0.5).all(axis=1)
+    assert low.sum() >= 2, owner_z[:, first]
+    np.testing.assert_array_equal(dbg["sampled"][:n].cpu().numpy()[low], first)
+    eng.close()
