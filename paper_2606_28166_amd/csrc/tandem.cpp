@@ -176,9 +176,10 @@ tandem_status check_cap(const tandem_capacity* cap, std::string* err) {
   return TANDEM_OK;
 }
 
-// Without a packed copy, narrow FFNs give the fused gate/up + SwiGLU GEMM too
-// few output tiles to fill the device: those run as a split-K GEMM over the
-// 2 ffn gate and up rows plus a SwiGLU pass over the summed partials.
+// Narrow FFNs may give the fused gate/up + SwiGLU GEMM too few output tiles to
+// fill the device (without a packed copy always, see gate_up): those run as a
+// split-K GEMM over the 2 ffn gate and up rows plus a SwiGLU pass over the summed
+// partials.
 bool split_gate_up(const tandem_model_cfg* c) {
   return c->weight_dtype == TANDEM_BF16 && c->d_model % 64 == 0 && c->ffn_dim < 8192;
 }
@@ -469,24 +470,31 @@ tandem_status gate_up(tandem_handle* h, const Model& m, const Layer& L, int M, h
     return TANDEM_OK;
   }
   // More rows: the tiled GEMM.  On the packed (pair-interleaved) copy SwiGLU is
-  // its epilogue, for every width: a split-K GEMM over the 2 ffn rows would
-  // write four times the bytes and need a pass over them (small pair: prefill
-  // of 8212 rows 7.34 -> 7.01 ms, 256-row steps 0.966 -> 0.922 ms, 1024-row
-  // steps 1.79 -> 1.77 ms).
+  // its epilogue: a split-K GEMM over the 2 ffn rows would write four times the
+  // bytes and need a pass over them (small pair: prefill of 8212 rows 7.34 -> 7.01
+  // ms, 256-row steps 0.966 -> 0.922 ms, 1024-row steps 1.79 -> 1.77 ms).  Except
+  // where its tiles leave half of the device idle over a long K, which the slices
+  // fill.  Steps of four layers, us, fused / split (d_model / ffn_dim, rows): 4096 /
+  // 2048, 256 rows 707 / 616; 4096 / 4096, 256 rows 743 / 691, 384 rows (192 tiles) 926 /
+  // 949; 3072 / 4096, 256 rows 581 / 545; 2048 / 4096, 256 rows 448 / 436; 2048 / 2048,
+  // 256 rows 377 / 383; 1536 / 4096, 256 rows 345 / 369.
   int S = 1;
   const bool pk = L.p_gate_up != nullptr && M > 64;
+  const bool a16 = pk && m.ffn16;
+  const long tiles = (long)((M + 127) / 128) * ((2 * F + 127) / 128);
+  const bool idle = 2 * tiles <= h->n_cu && d >= 2048 && d * tiles >= 1024L * h->n_cu;
   GemmArgs g{};
   g.dt = dt; g.A = m.xa; g.W = L.w_gate_up; g.M = M; g.K = d;
-  if (!pk && split_gate_up(&c)) {
+  g.Wp = pk ? L.p_gate_up : nullptr; g.a16 = a16;
+  if (split_gate_up(&c) && (!pk || idle)) {
     g.N = 2 * F; g.epi = EPI_PARTIAL;
     g.out = m.ws; g.ldo = 2 * F; g.split_stride = (long)M * 2 * F;
     g.splits = choose_splits(M, 2 * F, d, m.p.ws_floats, h->n_cu);
     TIMED(TANDEM_K_GEMM, launch_gemm(g, &S, st));
-    TIMED(TANDEM_K_OTHER, launch_swiglu_finish(m.ws, S, (long)M * 2 * F, M, F, false, false, m.xf, st));
+    TIMED(TANDEM_K_OTHER, launch_swiglu_finish(m.ws, S, (long)M * 2 * F, M, F, pk, a16, m.xf, st));
     return TANDEM_OK;
   }
   g.N = F; g.epi = EPI_SWIGLU;
-  g.Wp = pk ? L.p_gate_up : nullptr; g.a16 = pk && m.ffn16;
   g.out = (float*)m.xf; g.ldo = F; g.splits = 1;
   TIMED(TANDEM_K_GEMM, launch_gemm(g, &S, st));
   return TANDEM_OK;

@@ -3,8 +3,9 @@
 A prefill of M rows and the decode steps after it run every projection of a
 layer on the kernel that M selects: up to 128 rows the streaming GEMM, above it
 the tiled one over the packed weights (128 x 128, 128 x 256 and 256 x 256 tiles).
-The bar is the bf16 parity bound of the other cases: the kernels accumulate the
-same products in the same order of k, whatever the tile.
+The bar is the bf16 parity bound of the other cases: whatever the tile, the
+products are the same and their sums float32; only the order of the sums differs
+(the number of K slices depends on M and the grid, the row-major kernel permutes k).
 """
 import numpy as np
 import pytest
@@ -42,6 +43,21 @@ def test_projection_tile_edges(n_prompts, group, prompt_len, vocab, rows):
     p = P.run(_small(n_prompts, group, prompt_len, vocab), logits_at=(1, 2), seq_subset=rows)
     P.check(p, P.TOL_BF16)
     assert np.isfinite(p.out["logprob"]).all()
+
+
+# gate/up of the tiled GEMM.  An FFN that is not a multiple of 256 has no packed
+# down matrix, so its activations stay in split format: 128 x 128 tiles with a short
+# and a deep ring, 128 x 256 tiles.  2048 / 4096: K slices and a SwiGLU pass (fp16, and
+# split format where the FFN is 4080).
+@pytest.mark.parametrize("d,ffn,n_prompts,prompt_len", [
+    (256, 272, 2, 66), (512, 272, 1, 130), (256, 4112, 8, 66), (2048, 4096, 2, 66), (2048, 4080, 1, 257)])
+def test_gate_up_routes(d, ffn, n_prompts, prompt_len):
+    P.log(f"case gate/up: d_model {d}, ffn {ffn}, {n_prompts} prompts of {prompt_len} tokens")
+    wl = _small(n_prompts, 1, prompt_len, vocab=512)
+    for m in (wl.senior, wl.junior):
+        m.d_model, m.ffn_dim, m.n_q_heads, m.n_kv_heads = d, ffn, 4, 2
+    p = P.run(wl, logits_at=(1, 2))
+    P.check(p, P.TOL_BF16)
 
 
 # the float32 pair: up to 32 rows on the few-row kernel (4 or 8 rows at a time),
