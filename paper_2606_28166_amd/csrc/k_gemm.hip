@@ -653,7 +653,7 @@ hipError_t run_tile(const GemmArgs& a, int S, int cps, hipStream_t st) {
 }
 
 // Packed weights take the tile with the least estimated time: rounds of
-// workgroups over the 256 compute units times the time of a round, in units of
+// workgroups over the compute units times the time of a round, in units of
 // 128 x 128 results per compute unit at the largest tile's rate.  A round of
 // 128 x 256 fp16 tiles takes 2.2, one of 128 x 128 tiles (two workgroups per
 // unit) 2.45, a half-filled one 1.67 (us for 256 x 256, 128 x 256 and
@@ -667,10 +667,10 @@ hipError_t dispatch_tile(const GemmArgs& a, int S, int cps, hipStream_t st) {
   const int rows = EPI == EPI_SWIGLU ? 2 * a.N : a.N;
   auto tiles = [&](int bm, int bn) { return (long)((a.M + bm - 1) / bm) * ((rows + bn - 1) / bn) * S; };
   auto rounds = [](long t, long per) { return (double)((t + per - 1) / per); };
-  const long t128 = tiles(128, 128);
+  const long t128 = tiles(128, 128), cu = a.n_cu;
   if (a.a16) {
-    const double c128 = t128 <= 256 ? 1.67 : 2.45 * rounds(t128, 512);
-    const double cw = 2.2 * rounds(tiles(128, 256), 256), c256 = 4.0 * rounds(tiles(256, 256), 256);
+    const double c128 = t128 <= cu ? 1.67 : 2.45 * rounds(t128, 2 * cu);
+    const double cw = 2.2 * rounds(tiles(128, 256), cu), c256 = 4.0 * rounds(tiles(256, 256), cu);
     if (c256 <= cw && c256 <= c128) {
       // the XCD order pays where a tile reads much more than it writes (gate/up
       // of 8176 rows, K = 2560: 743 -> 721 us) or few tile rows share the
@@ -682,12 +682,12 @@ hipError_t dispatch_tile(const GemmArgs& a, int S, int cps, hipStream_t st) {
     if (cw < c128) return run_tile<128, 256, 1, 4, EPI, true, 1, true>(a, S, cps, st);
     return run_tile<128, 128, 2, 5, EPI, true, 2, true>(a, S, cps, st);
   }
-  const double c128 = t128 <= 256 ? 0.9 : 1.13 * rounds(t128, 512);
-  if (rounds(tiles(128, 256), 256) < c128) return run_tile<128, 256, 2, 4, EPI, false, 1, true>(a, S, cps, st);
+  const double c128 = t128 <= cu ? 0.9 : 1.13 * rounds(t128, 2 * cu);
+  if (rounds(tiles(128, 256), cu) < c128) return run_tile<128, 256, 2, 4, EPI, false, 1, true>(a, S, cps, st);
   // at most one 128 x 128 tile per compute unit: a deep ring where the K slice
   // has the chunks for it (QKV of 1024 small rows, 16 chunks: 13.7 -> 11.5 us;
   // O of 4056 rows, 32 chunks: 30.3 -> 24.2; O of 1024 rows, 8 chunks: 10.6, 12.4)
-  if (t128 <= 256 && 2 * cps >= 16) return run_tile<128, 128, 2, 6, EPI, false, 1, true>(a, S, cps, st);
+  if (t128 <= cu && 2 * cps >= 16) return run_tile<128, 128, 2, 6, EPI, false, 1, true>(a, S, cps, st);
   return run_tile<128, 128, 2, 3, EPI, false, 2, true>(a, S, cps, st);
 }
 
@@ -753,9 +753,13 @@ hipError_t launch_gemm(const GemmArgs& a, int* splits_used, hipStream_t st) {
       default: return dispatch_mfma<EPI_SWIGLU>(a, S, cps, st);
     }
   }
-  // A few rows of a float32 model whose rows of K are not long: above, the tiles'
-  // reuse and their K slices weigh more than the round trips.  Rows start 16-byte
-  // aligned where K % 4 == 0.
+  // A few rows of a float32 model whose rows of K are not long.  Steps of two layers
+  // of d_model = ffn_dim = 1024 and a vocabulary of 32000 (d_model 512), us, tiles /
+  // these rows: 1 row 394 / 149 (247 / 116), 4 rows 402 / 170 (252 / 135), 8 rows 408 /
+  // 245 (257 / 183), 16 rows 426 / 273 (269 / 201), 32 rows 469 / 331 (298 / 234).  The
+  // weights are read once per 8 rows, so the gain shrinks with the rows; more rows and
+  // longer K were not measured and stay with the tiles.  Rows start 16-byte aligned
+  // where K % 4 == 0.
   if (a.dt != DT_BF16 && a.M <= kRowsMax && a.K % 4 == 0 && a.K <= kRowsMaxK &&
       (((uintptr_t)a.A | (uintptr_t)a.W) & 15u) == 0) {
     if (splits_used) *splits_used = 1;

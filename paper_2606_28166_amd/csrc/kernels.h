@@ -45,6 +45,7 @@ struct GemmArgs {
   int ldo;
   long split_stride;
   int splits;
+  int n_cu;               // compute units of the device (the tile choice)
 };
 hipError_t launch_gemm(const GemmArgs& a, int* splits_used, hipStream_t st);
 

@@ -440,7 +440,7 @@ tandem_status gemm(tandem_handle* h, const Model& m, const void* A, const void* 
   GemmArgs g{};
   g.dt = dt; g.A = A; g.W = W; g.M = M; g.N = N; g.K = K; g.epi = epi;
   g.Wp = Wp; g.a16 = a16;                  // prefill-sized products read the packed copy too
-  g.out = out; g.ldo = N; g.split_stride = (long)M * N;
+  g.out = out; g.ldo = N; g.split_stride = (long)M * N; g.n_cu = h->n_cu;
   g.splits = epi == EPI_PARTIAL ? choose_splits(M, N, K, m.p.ws_floats, h->n_cu) : 1;
   TIMED(TANDEM_K_GEMM, launch_gemm(g, S, st));
   return TANDEM_OK;
@@ -485,7 +485,7 @@ tandem_status gate_up(tandem_handle* h, const Model& m, const Layer& L, int M, h
   const bool idle = 2 * tiles <= h->n_cu && d >= 2048 && d * tiles >= 1024L * h->n_cu;
   GemmArgs g{};
   g.dt = dt; g.A = m.xa; g.W = L.w_gate_up; g.M = M; g.K = d;
-  g.Wp = pk ? L.p_gate_up : nullptr; g.a16 = a16;
+  g.Wp = pk ? L.p_gate_up : nullptr; g.a16 = a16; g.n_cu = h->n_cu;
   if (split_gate_up(&c) && (!pk || idle)) {
     g.N = 2 * F; g.epi = EPI_PARTIAL;
     g.out = m.ws; g.ldo = 2 * F; g.split_stride = (long)M * 2 * F;
