@@ -185,7 +185,7 @@ PMC_STEPS = 24
 # kernel classes of the decode step at the Qwen shapes (128 rows): (name,
 # kernel-name substring, source file)
 PMC_CLASSES = (("attention", "attn_rows_kernel", "k_attn.hip"),
-               ("qkv_o", "gemm_stream_kernel<4, 4, false, 0>", "k_stream.hip"),
+               ("qkv_o", "gemm_stream_kernel<4, 2, false, 0>", "k_stream.hip"),
                ("ffn_partial", "gemm_stream_kernel<4, 4, true, 0>", "k_stream.hip"),
                ("gate_up_swiglu", "gemm_stream_kernel<4, 4, true, 2>", "k_stream.hip"),
                ("lm_heads", "gemm_stream_kernel<4, 4, true, 3>", "k_stream.hip"),
@@ -273,14 +273,14 @@ def pmc_run(warm: int = PMC_WARM) -> None:
 def class_weight_bytes(wl: W.Workload) -> dict:
     """Weight bytes each streaming-GEMM class of one decode step reads, both
     models (bf16): split-activation QKV and O; the fp16 split-K products (the
-    down projections, and the gate/up of an FFN narrower than 8192); the
-    gate/up products with the SwiGLU epilogue; the two LM heads."""
+    down projections); the gate/up products, whose plan has one K slice and the
+    SwiGLU epilogue in both models; the two LM heads."""
     out = {"qkv_o": 0, "ffn_partial": 0, "gate_up_swiglu": 0, "lm_heads": 0}
     for s in (wl.senior, wl.junior):
         d, hd, F = s.d_model, s.head_dim, s.ffn_dim
         out["qkv_o"] += 2 * s.n_layers * (d * (s.n_q_heads + 2 * s.n_kv_heads) * hd + s.n_q_heads * hd * d)
         out["ffn_partial"] += 2 * s.n_layers * F * d
-        out["ffn_partial" if F < 8192 else "gate_up_swiglu"] += 2 * s.n_layers * 2 * F * d
+        out["gate_up_swiglu"] += 2 * s.n_layers * 2 * F * d
         out["lm_heads"] += 2 * s.vocab * d
     return out
 
