@@ -20,9 +20,9 @@
 // written once more than with a count pass ahead of everything, but that pass
 // needed a ticket to find the last partial sum, and its release and acquire in
 // every workgroup were most of the time.  Both launches, 128 rollouts of at most
-// 3000 positions: 18.4 -> 7.8 us; a call at 512 x 4096 59.6 -> 18.2 us, at 2048 x
-// 4096 257 -> 35 us, at 8 rows of a million 855 -> 242 us (the smaller ones by then
-// bound by the host's 17 us).
+// 3000 positions: 18.4 -> 7.8 us.  Calls in a row, that kernel pair / these: 128 x 3000
+// 18.3 / 16.9 us, 512 x 4096 58.9 / 17.0 (both bound by the host's 17 us), 2048 x 4096
+// 242 / 41, 8 rows of a million 1251 / 269.
 #include <mutex>
 
 #include "common.h"

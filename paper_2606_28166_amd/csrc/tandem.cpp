@@ -655,8 +655,8 @@ tandem_status forward(tandem_handle* h, int i, const FwdRows& fr, bool lm_head, 
 // full depth, 128 rows, ms per step with turns / without / with turns that pass
 // only after the FFN-input norm: 5.64 / 5.77 / 5.90 at 300 positions, 10.27 /
 // 10.48 / 10.38 at 1100.  A smaller grid leaves compute units free, and the
-// edges between the streams (about 5 us each) only cost: 32 rows 3.73 with,
-// 3.70 without; 64 rows of the small pair 0.575 with, 0.559 without.  Prompt
+// edges between the streams (about 5 us each) only cost: 32 rows 3.46 with,
+// 3.42 without; 64 rows of the small pair 0.501 with, 0.474 without.  Prompt
 // rows take no turns either (ragged prompts of the small pair 7.44 with, 7.34
 // without).
 //
