@@ -33,6 +33,8 @@ CASES = [
     (2, 1, 1030, 32000, [1]),            # 2058 rows: 256 x 256 tiles with a ragged last row
     (5, 26, 9, 32001, [0, 70, 129]),     # 40 rows; steps of 130 rows, logits of an odd vocabulary in tiles
     (3, 43, 3, 32000, [5, 128]),         # steps of 129 rows, logits of a 128 x 256 tiled head
+    (2, 2, 18, 32000, None),             # steps of 4 rows, the most with a row's SwiGLU along a lane's elements
+    (5, 1, 18, 32000, None),             # steps of 5 rows
     (3, 32, 3, 31972, [5, 95]),          # steps of 96 rows, a last vocabulary block of 4 entries
 ]
 
